@@ -10,6 +10,7 @@
 #include <thread>
 #include <vector>
 
+#include "fold.hpp"
 #include "kernels.hpp"
 #include "opgen.hpp"
 
@@ -68,6 +69,10 @@ struct Ops {
     // stored piece by piece, so that the mixed kernel's copy of four pieces
     // of a row tile reads one contiguous kilobyte); forward and adjoint
     double *m2l64 = nullptr, *am2l64 = nullptr;
+    // FP64 form, uniform tree: the folded M2L's tables (fold.hpp), forward and
+    // adjoint, and its orders
+    double *fold64 = nullptr, *afold64 = nullptr;
+    FoldDev fold{};
     uint16_t *m2lbf = nullptr, *am2lbf = nullptr;
     size_t bf_part = 0;  // elements per bf16 (and binary16) part
     // binary16 encoding: a_r T rho_c in two binary16 parts, same layout as
@@ -198,6 +203,29 @@ fmm_status build_ops(int p, Ops **out) {
     }
     UP64(m2l64, f64) UP64(am2l64, af64) UP64(m2lbf, fbf) UP64(am2lbf, afbf)
     UP64(cls, cls)
+    {
+        FoldHost fh;
+        fold_host(p, fh);
+        for (int adj = 0; adj < 2; ++adj) {
+            const std::vector<double> &src = adj ? af64 : f64;
+            for (int od = 0; od < kFoldOrbits; ++od) {
+                const uint32_t e3 = fh.orbits[od];
+                const size_t id = id316_of(e3 & 3, (e3 >> 2) & 3, (e3 >> 4) & 3);
+                for (size_t rp = 0; rp < fh.rows.size(); ++rp)
+                    for (int kp = 0; kp < S; ++kp)
+                        if (fh.rows[rp] >= 0 && fh.kperm[kp] >= 0)
+                            fh.table[fold_place(p, fh, od, (int)rp, kp)] =
+                                src[(id * R + fh.rows[rp]) * S + fh.kperm[kp]];
+            }
+            if (adj) {
+                UP64(afold64, fh.table)
+            } else {
+                UP64(fold64, fh.table)
+            }
+        }
+        UP64(fold.orbits, fh.orbits) UP64(fold.kap, fh.kap)
+        UP64(fold.rows, fh.rows) UP64(fold.kperm, fh.kperm)
+    }
     {
         // binary16 tables: columns scaled by the harmonic size rho_c of their
         // degree (the multipoles are divided by it), each row by the power of
@@ -458,7 +486,8 @@ WorkSizes work_sizes(const fmm_tree *t, bool far) {
         const size_t g = ((size_t)1 << l) + 6;
         z.pack[l] = g * g * g * S * (f64 ? 8 : 4);
     }
-    z.m2lpart = m2l_partial_bytes(P, L, f64, t->ncu);
+    z.m2lpart = m2l_partial_bytes(P, L, t->ncu);
+    if (f64) z.m2lpart = m2l_fold_partial_bytes(P, L, t->ncu, z.m2lpart);
     if (m2l_half(t->cfg)) z.lmax = sizeof(uint32_t) * kLevelSlots;
     return z;
 }
@@ -721,7 +750,10 @@ fmm_status run_chain(fmm_tree *t, const Work &w, const void *charges, bool adjoi
                 pk.out[i] = w.pack[l];
                 pk.row0[i + 1] = pk.row0[i] + g * g;
             }
-            HIPCHK(launch_pack(P, f64, pk, st));
+            if (f64 && !t->cfg.m2l_rotation)
+                HIPCHK(launch_fold_pack(P, pk, o->fold, st));
+            else
+                HIPCHK(launch_pack(P, f64, pk, st));
         }
         CHK(rec(t, 4, st));
         if (side) CHK(fork_near());
@@ -739,12 +771,14 @@ fmm_status run_chain(fmm_tree *t, const Work &w, const void *charges, bool adjoi
                 if (!o->rot64) return fail(FMM_EDEVICE, "internal: no rotation tables");
                 HIPCHK(launch_m2l_rot(P, L, Bp, Lp, adjoint ? o->arot64 : o->rot64,
                                       adjoint ? o->atz64 : o->tz64, o->cls, st));
+            } else if (f64) {  // dense products, the offsets folded by reflections
+                HIPCHK(launch_m2l_fold(P, L, Bp, Lp, adjoint ? o->afold64 : o->fold64, o->fold, w.m2lpart,
+                                       w.m2lpart_bytes, t->ncu, m2l_partial_bytes(P, L, t->ncu), st));
             } else {  // dense products grouped by offset on the matrix cores
-                const void *A = f64    ? (const void *)(adjoint ? o->am2l64 : o->m2l64)
-                                : half ? (const void *)(adjoint ? o->am2lh : o->m2lh)
-                                       : (const void *)(adjoint ? o->am2lbf : o->m2lbf);
+                const void *A = half ? (const void *)(adjoint ? o->am2lh : o->m2lh)
+                                     : (const void *)(adjoint ? o->am2lbf : o->m2lbf);
                 const M2LHalf hv{w.lmax, adjoint ? o->aoscale : o->oscale};
-                HIPCHK(launch_m2l(P, L, f64, nsplit, Bp, Lp, of64, A, o->bf_part, o->cls, w.m2lpart,
+                HIPCHK(launch_m2l(P, L, nsplit, Bp, Lp, of64, A, o->bf_part, o->cls, w.m2lpart,
                                   w.m2lpart_bytes, t->ncu, half ? &hv : nullptr, st));
             }
         }

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/fmm.h"
 
 namespace fmm {
@@ -155,6 +157,34 @@ __device__ inline void unpack_rec(const double4 r, double &x, double &y, double 
 // stale read only lets an atomic through) skips its atomic.
 __device__ __forceinline__ void atomic_max_shared(unsigned int *p, unsigned int v) {
     if (v > __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p, v);
+}
+
+// Uniform selection from the per-level kernel-argument arrays (an unrolled
+// select chain: indexing them with a runtime value would copy the whole
+// argument struct to scratch memory).
+template <typename T, int N>
+__device__ inline T pick(const T (&a)[N], int i) {
+    T v = a[0];
+#pragma unroll
+    for (int j = 1; j < N; ++j)
+        if (i == j) v = a[j];
+    return v;
+}
+
+// Workgroup barrier with this wave's LDS operations complete.  Written as one asm
+// statement with a memory clobber so that the compiler moves no memory
+// access across it and adds no wait of its own for the global loads still
+// in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
 }
 
 // The last step of an evaluation for sorted particle i (Sec. 2.1, S11):

@@ -1,6 +1,7 @@
 // kernels.hpp -- launchers of the device kernels (all asynchronous on `st`).
 #pragma once
 #include <algorithm>
+#include <vector>
 
 #include "common.hpp"
 
@@ -235,12 +236,54 @@ hipError_t ad_launch_p2p(int64_t max_units, const uint32_t *nunits, const int2 *
 // (FMM_NOALLOC_SCRATCH_BYTES), looked up on the first call per device
 hipError_t noalloc_scratch(void **ptr);
 
-// m2l.hip: every level 2..L in one launch; B[l], Lc[l] indexed by level.
-// Mixed form: A = bf16 operator parts spaced astride elements apart (layout
-// [part][317][R/16][S/8][16][8]), B[l] = FP32 padded multipole grid.  Both
-// forms cut the small levels into K parts: `partial` >= m2l_partial_bytes()
-// of FP64 scratch.
-size_t m2l_partial_bytes(int P, int L, bool f64, int ncu);
+// m2l_fold.hip: the FP64 form's M2L, its offsets folded by reflections
+// (fold.hpp).  The tiles of all levels are one list; the last ones are cut
+// into parts of their steps where that fills the chip, their FP64 partial
+// sums bounded by `cap` bytes.
+constexpr int kFoldMaxLev = FMM_MAX_LEVEL - 1;
+constexpr int kFoldParts = 64;
+struct FoldPlan {
+    int tile;                 // targets of a tile
+    int64_t nfull;            // whole tiles
+    int nrest, nsplit;        // the remaining tiles and their parts
+    uint16_t cut[kFoldParts + 1];  // first step (chunk, orbit) of each part
+    int nlev;
+    int level[kFoldMaxLev];   // the levels, largest first
+    int64_t tile0[kFoldMaxLev];    // first tile of each level
+    const double *B[kFoldMaxLev];  // padded operand grid of the level, in K order
+    double *L[kFoldMaxLev];
+};
+size_t m2l_fold_partial_bytes(int P, int L, int ncu, size_t cap);
+// host tables of order P: K order, its parities in pairs, row order, the
+// orbits (2 bits a component) and room for one operator table, filled at
+// fold_place()
+struct FoldHost {
+    std::vector<int16_t> kperm, rows;
+    std::vector<uint16_t> kap;
+    std::vector<uint32_t> orbits;
+    std::vector<int2> row_place;
+    std::vector<double> table;
+};
+void fold_host(int P, FoldHost &h);
+// where entry (row position, K position) of orbit o's matrix is stored
+size_t fold_place(int P, const FoldHost &h, int o, int rowpos, int kpos);
+struct FoldDev {
+    const uint32_t *orbits;
+    const uint16_t *kap;
+    const int16_t *rows, *kperm;
+};
+// FP64 multipoles of every level into its padded operand grid, in K order
+hipError_t launch_fold_pack(int P, const PackPlan &pl, const FoldDev &fd, hipStream_t st);
+// every level 2..L in one launch; B[l], Lc[l] indexed by level
+hipError_t launch_m2l_fold(int P, int L, void *const *B, void *const *Lc, const double *A, const FoldDev &fd,
+                           double *partial, size_t partial_bytes, int ncu, size_t cap, hipStream_t st);
+
+// m2l.hip, mixed form: every level 2..L in one launch; B[l], Lc[l] indexed
+// by level.  A = bf16 operator parts spaced astride elements apart (layout
+// [part][317][R/16][S/8][16][8]), B[l] = FP32 padded multipole grid.  The
+// small levels are cut into K parts: `partial` >= m2l_partial_bytes() of FP64
+// scratch.
+size_t m2l_partial_bytes(int P, int L, int ncu);
 constexpr int kMixedSplit3PMax = 13;  // LDS holds the 3-part operator ring up to p = 13
 // The 2-part bf16 split (about 16 bits per operand) keeps the mixed force
 // within 1e-6 of the FP64 form up to p = 10 only (measured 1.2e-6 at
@@ -255,8 +298,7 @@ struct M2LHalf {
     const uint32_t *lmax;   // per-level maxima (by level) of the scaled multipoles
     const float *oscale;    // [S]
 };
-hipError_t launch_m2l(int P, int L, bool f64, int nsplit, void *const *B, void *const *Lc,
-                      const int *out_f64, const void *A, size_t astride, const int2 *cls,
+hipError_t launch_m2l(int P, int L, int nsplit, void *const *B, void *const *Lc, const int *out_f64, const void *A, size_t astride, const int2 *cls,
                       double *partial, size_t partial_bytes, int ncu, const M2LHalf *half,
                       hipStream_t st);
 

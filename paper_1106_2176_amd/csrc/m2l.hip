@@ -1,4 +1,5 @@
-// m2l.hip -- multipole-to-local translation on the matrix cores.
+// m2l.hip -- the mixed form's multipole-to-local translation on the matrix
+// cores, and the FP64 form's by rotation (its dense one: m2l_fold.hip).
 //
 // M2L is the one dense contraction of the method (Sec. 3.1: P2P and M2L are
 // the two dominant kernels; Sec. 5: M2L runs at every level with no
@@ -20,12 +21,10 @@
 // (operators once at set-up, multipoles in registers from FP32); the
 // products x_i y_j with i + j < parts are accumulated by
 // v_mfma_f32_16x16x32_bf16 in FP32 and merged into FP64 accumulators every
-// 256 K terms.  Plain form: v_mfma_f64_16x16x4_f64.
+// 256 K terms.
 // MFMA operand layout (16 x 16 tiles, 64 lanes): A lane l holds row l%16,
-// K-group l/16; B lane l holds column l%16, K-group l/16.  Results: for the
-// bf16 instruction lane l holds rows 4(l/16) .. 4(l/16)+3 of column l%16; for
-// the FP64 instruction lane l, item i holds row l/16 + 4i of column l%16
-// (both layouts measured on gfx950).
+// K-group l/16; B lane l holds column l%16, K-group l/16; the result lane l
+// holds rows 4(l/16) .. 4(l/16)+3 of column l%16 (measured on gfx950).
 #include <algorithm>
 #include <map>
 #include <mutex>
@@ -90,18 +89,6 @@ struct M2LUnit {
     int64_t pbase;  // first parent (Morton) of the tile
 };
 
-// Uniform selection from the per-level kernel-argument arrays (an unrolled
-// select chain: indexing them with a runtime value would copy the whole
-// argument struct to scratch memory).
-template <typename T, int N>
-__device__ inline T pick(const T (&a)[N], int i) {
-    T v = a[0];
-#pragma unroll
-    for (int j = 1; j < N; ++j)
-        if (i == j) v = a[j];
-    return v;
-}
-
 __device__ inline int find_level(const int64_t (&first)[kMaxLev + 1], int nlev, int64_t b) {
     int li = 0;
 #pragma unroll
@@ -160,14 +147,6 @@ __device__ __forceinline__ void wait_vm() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// Workgroup barrier with this wave's LDS reads complete.  Written as one asm
-// statement with a memory clobber so that the compiler moves no memory
-// access across it and adds no wait of its own for the global loads still
-// in flight (the operator ring is synchronised by the explicit vmcnt waits).
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -214,14 +193,6 @@ __device__ __forceinline__ f32x4 mfma32(const bf16x8 a, const bf16x8 b, const f3
                                                        __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     else
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, N>(f);
-    }
 }
 
 template <int NSPLIT, int P, int NW>
@@ -594,156 +565,6 @@ __global__ __launch_bounds__(256) void k_m2l_fixup(int P, M2LPlan pl, const doub
         ((float *)pick(pl.L, li))[trow * S + row] = (float)v;
 }
 
-// ------------------------------------------------------------ plain form
-// FP64 operators [317][R][S] and the FP64 padded multipole grid.  K runs over
-// the 189 offsets x S coefficients (entries past p^2 are zero in both), in
-// chunks of 8 that never straddle an offset, so a chunk's operator and
-// source shift are uniform over the block.  A chunk: R x 8 operator values
-// staged in LDS (each thread loads EPT of them one chunk ahead, two register
-// sets), then per wave RT x NB x 2 MFMAs (v_mfma_f64_16x16x4_f64, lane group
-// q takes K index 4 j + q of the chunk).  Registers fit two blocks per CU up
-// to p = 11 (one beyond).
-template <int P, int WPE = (P <= 11 ? 2 : 1)>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void k_m2l_f64(
-    M2LPlan pl, const double *__restrict__ A, const int2 *__restrict__ cls,
-    double *__restrict__ partial) {
-    constexpr int P2 = P * P, S = coef_stride(P), RT = m2l_rows(P) / 16, R = RT * 16;
-    constexpr int NB = 2, KC = 8, ROWP = KC + 1, CPO = S / KC;  // chunks per offset
-    constexpr int NEL = R * KC, EPT = (NEL + 255) / 256;
-    constexpr int NCH = kOffsetsPerClass * CPO;
-    __shared__ double As[2][R * ROWP];
-    __shared__ int sA[kOffsetsPerClass], sB[kOffsetsPerClass];
-
-    const M2LUnit u = m2l_unit(pl);
-    const int l = u.l, k = u.k;
-    const double *__restrict__ B = (const double *)pick(pl.B, u.li);
-    const int n = 1 << l, h = n >> 1;
-    const int64_t G = n + 6;
-    const int64_t npar = (int64_t)h * h * h;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = lane >> 4, col = lane & 15;
-    const int nsplit = pick(pl.nsplit, u.li);
-    const int kbeg = (int)((int64_t)u.part * NCH / nsplit);
-    const int kend = (int)((int64_t)(u.part + 1) * NCH / nsplit);
-
-    for (int i = tid; i < kOffsetsPerClass; i += 256) {
-        const int2 e = cls[k * kOffsetsPerClass + i];
-        sA[i] = e.y * R * S;
-        sB[i] = (int)unpack_delta(e.x, G) * S;
-    }
-    int64_t tpad[NB], trow[NB];
-    bool cvalid[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int64_t pid = u.pbase + wave * NB * 16 + b * 16 + col;
-        cvalid[b] = pid < npar;
-        target_of(cvalid[b] ? pid : 0, k, n, G, S, tpad[b], trow[b]);
-    }
-    __syncthreads();
-
-    // this thread's elements of an A chunk: (row, kk) = (e / KC, e % KC)
-    auto load_a = [&](int kc, double (&dst)[EPT]) __attribute__((always_inline)) {
-        const int slot = kc / CPO, c0 = KC * (kc - slot * CPO);
-        const double *a = A + sA[slot] + c0;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + 256 * i;
-            dst[i] = (NEL % 256 == 0 || e < NEL) ? a[(e / KC) * S + e % KC] : 0.0;
-        }
-    };
-    auto store_a = [&](int buf, const double (&src)[EPT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + 256 * i;
-            if (NEL % 256 == 0 || e < NEL) As[buf][(e / KC) * ROWP + e % KC] = src[i];
-        }
-    };
-    auto load_b = [&](int kc, double (&dst)[2][NB]) __attribute__((always_inline)) {
-        const int slot = kc / CPO, c0 = KC * (kc - slot * CPO);
-        const int64_t off = sB[slot] + c0 + q;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) dst[j][b] = B[tpad[b] + off + 4 * j];
-    };
-
-    f64x4 acc[RT][NB];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int b = 0; b < NB; ++b) acc[r][b] = f64x4{0, 0, 0, 0};
-
-    // step t = kc - kbeg: chunk kc is in LDS buffer t & 1, chunk kc + 1 in
-    // register set t & 1 and chunk kc + 2 in the other (the last chunk is
-    // loaded again past the end of the range)
-    double ar[2][EPT], br[2][2][NB], bc[2][NB];
-    load_a(kbeg, ar[0]);
-    store_a(0, ar[0]);
-    load_b(kbeg, bc);
-    load_a(min(kbeg + 1, kend - 1), ar[0]);
-    load_b(min(kbeg + 1, kend - 1), br[0]);
-    load_a(min(kbeg + 2, kend - 1), ar[1]);
-    load_b(min(kbeg + 2, kend - 1), br[1]);
-    __syncthreads();
-    auto chunk = [&](int kc, auto pc) __attribute__((always_inline)) {
-        constexpr int ph = decltype(pc)::value;  // (kc - kbeg) & 1
-        const double *as = As[ph];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const double av = as[(16 * r + col) * ROWP + 4 * j + q];
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    acc[r][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bc[j][b], acc[r][b], 0, 0, 0);
-            }
-        store_a(ph ^ 1, ar[ph]);  // chunk kc + 1 into the other buffer, read by
-                                  // every wave up to the last barrier
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) bc[j][b] = br[ph][j][b];
-        load_a(min(kc + 3, kend - 1), ar[ph]);
-        load_b(min(kc + 3, kend - 1), br[ph]);
-        __syncthreads();
-    };
-    // a pair of chunks per pass keeps the parity a compile-time constant
-    int kc = kbeg;
-    for (; kc + 1 < kend; kc += 2) {
-        chunk(kc, std::integral_constant<int, 0>{});
-        chunk(kc + 1, std::integral_constant<int, 1>{});
-    }
-    if (kc < kend) chunk(kc, std::integral_constant<int, 0>{});
-
-    // FP64 MFMA result layout: lane l, item i holds row l/16 + 4 i
-    if (nsplit == 1) {
-        double *Lout = (double *)pick(pl.L, u.li);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            if (!cvalid[b]) continue;
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * r + q + 4 * i;
-                    if (row < P2) Lout[trow[b] * S + row] = acc[r][b][i];
-                }
-        }
-    } else {
-        const int64_t slot = pick(pl.part0, u.li) + (int64_t)u.part * pick(pl.ntile, u.li) + u.tile;
-        double *dst = partial + slot * kTile * P2;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * r + q + 4 * i;
-                    if (row < P2) dst[(wave * NB * 16 + b * 16 + col) * P2 + row] = acc[r][b][i];
-                }
-    }
-}
-
 // ------------------------------------------------ rotation-based M2L (FP64)
 // O(p^3) per pair instead of O(p^4): the multipole of a source box is rotated
 // into the frame whose z axis points along the offset (target minus source),
@@ -1049,8 +870,7 @@ static M2LPlan make_plan(int P, int L, bool allow_split, int ncu) {
     return it->second;
 }
 
-size_t m2l_partial_bytes(int P, int L, bool f64, int ncu) {
-    (void)f64;  // both forms split the small levels and keep FP64 partial sums
+size_t m2l_partial_bytes(int P, int L, int ncu) {
     if (L < 2) return 0;
     const M2LPlan pl = make_plan(P, L, true, ncu);
     int64_t np = 0;
@@ -1080,8 +900,7 @@ static hipError_t fixup(int P, const M2LPlan &pl, unsigned nfix, const double *p
     return hipGetLastError();
 }
 
-hipError_t launch_m2l(int P, int L, bool f64, int nsplit, void *const *B, void *const *Lc,
-                      const int *out_f64, const void *A, size_t astride, const int2 *cls,
+hipError_t launch_m2l(int P, int L, int nsplit, void *const *B, void *const *Lc, const int *out_f64, const void *A, size_t astride, const int2 *cls,
                       double *partial, size_t partial_bytes, int ncu, const M2LHalf *half,
                       hipStream_t st) {
     if (L < 2) return hipSuccess;
@@ -1096,19 +915,8 @@ hipError_t launch_m2l(int P, int L, bool f64, int nsplit, void *const *B, void *
     }
     const unsigned nb = (unsigned)pl.unit0[pl.nlev];
     const unsigned nfix = (unsigned)pl.fix0[pl.nlev];
-    if (nfix > 0 && (!partial || partial_bytes < m2l_partial_bytes(P, L, f64, ncu)))
+    if (nfix > 0 && (!partial || partial_bytes < m2l_partial_bytes(P, L, ncu)))
         return hipErrorInvalidValue;
-    if (f64) {
-        switch (P) {
-#define CASE(PP) \
-    case PP: k_m2l_f64<PP><<<nb, 256, 0, st>>>(pl, (const double *)A, cls, partial); break;
-            CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
-            CASE(9) CASE(10) CASE(11) CASE(12) CASE(13) CASE(14) CASE(15) CASE(16)
-#undef CASE
-            default: return hipErrorInvalidValue;
-        }
-        return fixup(P, pl, nfix, partial, st);
-    }
     if (half) {
         if (!half->lmax || !half->oscale) return hipErrorInvalidValue;
         switch (P) {
