@@ -1167,155 +1167,6 @@ __global__ __launch_bounds__(64 * kAdP2PWaves) void k_ad_p2p(
                            rec, out, c);
 }
 
-// Gathered M2L (FP64 MFMA), added to the locals: the targets of each (level,
-// class) group, in tiles of 128 columns (4 waves x 2 x 16), against the K
-// range of the class's 189 slots x S coefficients in chunks of 8; a column's
-// source row for a slot comes from its V slots (an absent source reads the
-// zero row).  A chunk's
-// operator (R x 8, uniform over the block) is staged in LDS one chunk ahead;
-// lane group q takes K index 4 j + q of a chunk (v_mfma_f64_16x16x4_f64).
-template <int P>
-__global__ __launch_bounds__(256) void k_ad_m2l(AdM2LPlan pl, const double *__restrict__ A,
-                                                const int2 *__restrict__ cls, const double *__restrict__ M,
-                                                const int *__restrict__ vidx, int64_t box2,
-                                                const int *__restrict__ tgt, int64_t zero_row,
-                                                double *__restrict__ Lc, double *__restrict__ partial) {
-    constexpr int P2 = P * P, S = coef_stride(P), RT = m2l_rows(P) / 16, R = RT * 16;
-    constexpr int NB = 2, KC = 8, ROWP = KC + 1, CPO = S / KC;
-    constexpr int NEL = R * KC, EPT = (NEL + 255) / 256;
-    constexpr int NCH = kOffsetsPerClass * CPO;
-    __shared__ double As[2][R * ROWP];
-    __shared__ int sA[kOffsetsPerClass];
-    // block = part * units + tile: part takes chunks [kbeg, kend) of the K range
-    const int64_t part = blockIdx.x / pl.units, b = blockIdx.x - part * pl.units;
-    const int kbeg = (int)(part * NCH / pl.nsplit), kend = (int)((part + 1) * NCH / pl.nsplit);
-    int gi = 0;
-    for (int j = 1; j < pl.ngroups; ++j)
-        if (b >= pl.grp[j].unit0) gi = j;
-    const AdM2LGroup gr = pl.grp[gi];
-    const int64_t tile = b - gr.unit0;
-    const int k = gr.cls;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = lane >> 4, col = lane & 15;
-    for (int i = tid; i < kOffsetsPerClass; i += 256) sA[i] = cls[k * kOffsetsPerClass + i].y * R * S;
-    int64_t tbox[NB];
-    const int *vrow[NB];
-#pragma unroll
-    for (int bb = 0; bb < NB; ++bb) {
-        const int64_t c = tile * 128 + wave * NB * 16 + bb * 16 + col;
-        tbox[bb] = c < gr.count ? tgt[gr.toff + c] : -1;
-        vrow[bb] = tbox[bb] >= 0 ? vidx + (tbox[bb] - box2) * kOffsetsPerClass : nullptr;
-    }
-    __syncthreads();
-    auto load_a = [&](int kc, double (&dst)[EPT]) __attribute__((always_inline)) {
-        const int slot = kc / CPO, c0 = KC * (kc - slot * CPO);
-        const double *a = A + sA[slot] + c0;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + 256 * i;
-            dst[i] = (NEL % 256 == 0 || e < NEL) ? a[(e / KC) * S + e % KC] : 0.0;
-        }
-    };
-    auto store_a = [&](int buf, const double (&src)[EPT]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + 256 * i;
-            if (NEL % 256 == 0 || e < NEL) As[buf][(e / KC) * ROWP + e % KC] = src[i];
-        }
-    };
-    // source rows of the slot being fetched and of the next slot (its vidx
-    // load is issued a slot ahead, so that no fetch waits on it); load_b is
-    // called with a chunk index that never decreases and grows by at most one
-    int srow[NB], snext[NB], pslot = kbeg / CPO;
-#pragma unroll
-    for (int bb = 0; bb < NB; ++bb) {
-        srow[bb] = vrow[bb] ? vrow[bb][pslot] : -1;
-        snext[bb] = (vrow[bb] && pslot + 1 < kOffsetsPerClass) ? vrow[bb][pslot + 1] : -1;
-    }
-    auto load_b = [&](int kc, double (&dst)[2][NB]) __attribute__((always_inline)) {
-        const int slot = kc / CPO, c0 = KC * (kc - slot * CPO);
-        if (slot != pslot) {
-            pslot = slot;
-#pragma unroll
-            for (int bb = 0; bb < NB; ++bb) {
-                srow[bb] = snext[bb];
-                snext[bb] = (vrow[bb] && slot + 1 < kOffsetsPerClass) ? vrow[bb][slot + 1] : -1;
-            }
-        }
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb) {
-            const double *src = M + (srow[bb] >= 0 ? (int64_t)srow[bb] : zero_row) * S + c0 + q;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) dst[j][bb] = src[4 * j];
-        }
-    };
-    f64x4 acc[RT][NB];
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb) acc[r][bb] = f64x4{0, 0, 0, 0};
-    double ar[2][EPT], br[2][2][NB], bc[2][NB];
-    load_a(kbeg, ar[0]);
-    store_a(0, ar[0]);
-    load_b(kbeg, bc);
-    load_a(min(kbeg + 1, kend - 1), ar[0]);
-    load_b(min(kbeg + 1, kend - 1), br[0]);
-    load_a(min(kbeg + 2, kend - 1), ar[1]);
-    load_b(min(kbeg + 2, kend - 1), br[1]);
-    __syncthreads();
-    auto chunk = [&](int kc, auto pc) __attribute__((always_inline)) {
-        constexpr int ph = decltype(pc)::value;
-        const double *as = As[ph];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const double av = as[(16 * r + col) * ROWP + 4 * j + q];
-#pragma unroll
-                for (int bb = 0; bb < NB; ++bb)
-                    acc[r][bb] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bc[j][bb], acc[r][bb], 0, 0, 0);
-            }
-        store_a(ph ^ 1, ar[ph]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int bb = 0; bb < NB; ++bb) bc[j][bb] = br[ph][j][bb];
-        load_a(min(kc + 3, kend - 1), ar[ph]);
-        load_b(min(kc + 3, kend - 1), br[ph]);
-        __syncthreads();
-    };
-    int kc = kbeg;
-    for (; kc + 1 < kend; kc += 2) {
-        chunk(kc, std::integral_constant<int, 0>{});
-        chunk(kc + 1, std::integral_constant<int, 1>{});
-    }
-    if (kc < kend) chunk(kc, std::integral_constant<int, 0>{});
-    if (pl.nsplit == 1) {
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb) {
-            if (tbox[bb] < 0) continue;
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * r + q + 4 * i;
-                    if (row < P2) Lc[tbox[bb] * S + row] += acc[r][bb][i];
-                }
-        }
-    } else {  // this part's sums of the tile's 128 columns, summed by k_ad_m2l_sum
-        double *dst = partial + (part * pl.units + b) * 128 * P2;
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb)
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int row = 16 * r + q + 4 * i;
-                    if (row < P2) dst[(wave * NB * 16 + bb * 16 + col) * P2 + row] = acc[r][bb][i];
-                }
-    }
-}
-
 // The K-split parts of the gathered M2L added into the locals in part order
 // (one thread per (tile, column, row)).
 __global__ void k_ad_m2l_sum(AdM2LPlan pl, int P2, int S, const int *__restrict__ tgt,
@@ -1372,7 +1223,8 @@ __global__ __launch_bounds__(256) void k_ad_class(int64_t box2, int64_t nb, cons
 // factors and by a power of two per level, split likewise; three products
 // hi.hi + hi.lo + lo.hi on v_mfma_f32_16x16x32_f16, FP32 accumulation
 // merged into FP64 every 256 K terms), with the multipole operand gathered
-// through the V slots as in the FP64 kernel.
+// through the V slots: the targets of each (level, class) group in tiles of
+// 128 columns against the class's 189 slots.
 
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -1778,25 +1630,6 @@ hipError_t ad_launch_l2l(int P, int64_t b0, int64_t nb, const uint32_t *code, co
 #undef X
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t ad_launch_m2l(int P, const AdM2LPlan &pl, const double *A, const int2 *cls, const double *M,
-                         const int *vidx, int64_t box2, const int *tgt, int64_t zero_row, double *Lc, double *partial,
-                         hipStream_t st) {
-    if (pl.units == 0) return hipSuccess;
-    if (pl.nsplit < 1 || (pl.nsplit > 1 && !partial)) return hipErrorInvalidValue;
-    const unsigned nb = (unsigned)(pl.units * pl.nsplit);
-    switch (P) {
-#define X(PP) \
-    case PP: k_ad_m2l<PP><<<nb, 256, 0, st>>>(pl, A, cls, M, vidx, box2, tgt, zero_row, Lc, partial); break;
-        AD_CASES(X)
-#undef X
-        default: return hipErrorInvalidValue;
-    }
-    if (pl.nsplit > 1)
-        k_ad_m2l_sum<<<ad_blocks(pl.units * 128 * P * P, 256), 256, 0, st>>>(pl, P * P, coef_stride(P), tgt, partial,
-                                                                             Lc);
     return hipGetLastError();
 }
 

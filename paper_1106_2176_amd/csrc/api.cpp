@@ -64,13 +64,12 @@ struct Ops {
     // [8][P2][P2] input-major transfer tables
     double *up64 = nullptr, *down64 = nullptr, *aup64 = nullptr, *adown64 = nullptr;
     float *up32 = nullptr, *down32 = nullptr, *aup32 = nullptr, *adown32 = nullptr;
-    // M2L tables (316 operators + a zero one): FP64 [317][R][S], and three
-    // bf16 parts [3][317][R/16][S/8][16][8] for the mixed form (a 16-row tile
-    // stored piece by piece, so that the mixed kernel's copy of four pieces
-    // of a row tile reads one contiguous kilobyte); forward and adjoint
-    double *m2l64 = nullptr, *am2l64 = nullptr;
-    // FP64 form, uniform tree: the folded M2L's tables (fold.hpp), forward and
-    // adjoint, and its orders
+    // M2L tables (316 operators + a zero one) of the mixed form: three bf16
+    // parts [3][317][R/16][S/8][16][8] (a 16-row tile stored piece by piece,
+    // so that the mixed kernel's copy of four pieces of a row tile reads one
+    // contiguous kilobyte); forward and adjoint
+    // FP64 form: the folded M2L's tables (fold.hpp), forward and adjoint, and
+    // its orders
     double *fold64 = nullptr, *afold64 = nullptr;
     FoldDev fold{};
     uint16_t *m2lbf = nullptr, *am2lbf = nullptr;
@@ -201,7 +200,7 @@ fmm_status build_ops(int p, Ops **out) {
         split_bf16(af64[i], 3, pt);
         for (int k = 0; k < 3; ++k) afbf[k * nT + j] = pt[k];
     }
-    UP64(m2l64, f64) UP64(am2l64, af64) UP64(m2lbf, fbf) UP64(am2lbf, afbf)
+    UP64(m2lbf, fbf) UP64(am2lbf, afbf)
     UP64(cls, cls)
     {
         FoldHost fh;
@@ -224,7 +223,7 @@ fmm_status build_ops(int p, Ops **out) {
             }
         }
         UP64(fold.orbits, fh.orbits) UP64(fold.kap, fh.kap)
-        UP64(fold.rows, fh.rows) UP64(fold.kperm, fh.kperm)
+        UP64(fold.rows, fh.rows) UP64(fold.kperm, fh.kperm) UP64(fold.cls, fh.cls)
     }
     {
         // binary16 tables: columns scaled by the harmonic size rho_c of their
@@ -376,7 +375,8 @@ struct AdTree {
     int64_t off[FMM_MAX_LEVEL + 2] = {};      // first box of each level, off[depth + 1] = nbox
     int64_t nlist[3] = {};                    // items of U, W, X
     int64_t goff[8 * FMM_MAX_LEVEL + 1] = {}; // first target of each (level, class) group
-    AdM2LPlan plan{};
+    AdM2LPlan plan{};                         // mixed form
+    FoldPlan fold{};                          // FP64 form
     uint32_t *hbuf = nullptr;                 // pinned host words for the build's counts
     Buf code, ps, pe, parent, child, leaf, cmask, nchild, coff, lev, col, vidx, cnts, offs, iu, iw, ix,
         is_head, head, hoff, lbox, lstart, llev, tgt, ccnt, goffd, offd, ucnt, uoff, units, s27, units_m;
@@ -471,7 +471,8 @@ WorkSizes work_sizes(const fmm_tree *t, bool far) {
     if (t->ad) {  // FP64 coefficients by box id, plus the zero row
         z.farf = sizeof(double4) * (size_t)t->n;
         z.M[0] = z.Lc[0] = sizeof(double) * (size_t)(t->ad->nbox + 1) * S;
-        z.m2lpart = ad_m2l_partial_bytes(t->ad->plan, P);
+        z.m2lpart = f64 ? fold_partial_bytes(t->ad->fold, P) : ad_m2l_partial_bytes(t->ad->plan, P);
+        if (f64) z.pack[0] = sizeof(double) * (size_t)(t->ad->nbox + 1) * S;  // the multipoles in K order
         if (m2l_half(t->cfg)) {  // the binary16 parts of the multipoles, and the level maxima
             z.pack[0] = sizeof(float) * (size_t)(t->ad->nbox + 1) * S;
             z.lmax = sizeof(uint32_t) * kLevelSlots;
@@ -644,7 +645,12 @@ fmm_status work_from_scratch(fmm_tree *t, bool far, Work &w) {
             oM[l] = take(z.M[l]);
             oL[l] = take(z.Lc[l]);
         }
-        if (z.pack[l]) oP[l] = take(z.pack[l]);
+        // the adaptive tree's operands lie over the near and far partials
+        // where they fit: M2L ends before either is written
+        if (t->ad && z.pack[l] && z.pack[l] <= o_far + z.farf)
+            oP[l] = o_near;
+        else if (z.pack[l])
+            oP[l] = take(z.pack[l]);
     }
     if (off > (size_t)FMM_NOALLOC_SCRATCH_BYTES)
         return fail(FMM_EINVAL, "this tree's evaluation needs " + std::to_string(off) +
@@ -932,7 +938,9 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     CHK(ensure(t, a->is_head, u4 * n, st));
     CHK(ensure(t, a->head, u4 * n, st));
     CHK(ensure(t, a->hoff, u4 * (n + 1), st));
-    const int ngrp = 8 * std::max(nlev - 2, 0);
+    // (level, class) groups of the mixed form's M2L targets
+    const bool f64 = is_f64_form(t);
+    const int ngrp = f64 ? 0 : 8 * std::max(nlev - 2, 0);
     CHK(ensure(t, a->ccnt, u4 * std::max(ngrp, 1), st));
     int *lev = bp<int>(a->lev), *col = bp<int>(a->col), *vidx = bp<int>(a->vidx);
     uint32_t *nu = bp<uint32_t>(a->cnts), *nw = nu + n27, *nx = nw + n27;
@@ -941,7 +949,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     uint32_t *ou = bp<uint32_t>(a->offs), *ow = ou + nbox + 1, *ox = ow + nbox + 1;
     HIPCHK(hipMemcpyAsync(a->offd.p, a->off, sizeof(int64_t) * (nlev + 1), hipMemcpyHostToDevice, st));
     HIPCHK(ad_launch_structure(nbox, nlev, a->off, bp<int64_t>(a->offd), code, parent, child, lev, col,
-                               t->ops->cls, vidx, st));
+                               f64 ? t->ops->fold.cls : t->ops->cls, vidx, st));
     HIPCHK(ad_launch_lists(nbox, 0, lev, code, parent, col, child, leaf, nu, nw, nx, nullptr, nullptr, nullptr,
                            nullptr, nullptr, nullptr, st));
     HIPCHK(launch_scan(3 * n27, nu, su, scan, st));
@@ -1011,7 +1019,19 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     a->plan.nsplit = a->plan.units ? (int)std::min<int64_t>(8, std::max<int64_t>(1, (4 * t->ncu + a->plan.units - 1) /
                                                                                          a->plan.units))
                                    : 1;
-    if (at != a->nvbox) return fail(FMM_EDEVICE, "internal: M2L groups do not cover the boxes");
+    if (!f64 && at != a->nvbox) return fail(FMM_EDEVICE, "internal: M2L groups do not cover the boxes");
+    if (f64) {
+        // tiles of the folded M2L; its partial sums and the multipoles in K
+        // order together take at most min(8 T, max(1024, T)) tiles of 128
+        // targets' sums, T the tiles of 128 (about four parts per compute
+        // unit, and no parts above 1024 tiles)
+        const int tt = fold_tile_targets(c.p);
+        const int64_t T = (a->nvbox + 127) / 128;
+        const size_t sums = sizeof(double) * 128 * (size_t)c.p * c.p,
+                     pack = sizeof(double) * (size_t)(nbox + 1) * coef_stride(c.p),
+                     most = T < 1024 ? sums * (size_t)std::min<int64_t>(8 * T, 1024) : 0;
+        a->fold = fold_plan(c.p, (a->nvbox + tt - 1) / tt, t->ncu, most > pack ? most - pack : 0);
+    }
     if (ngrp) {
         CHK(ensure(t, a->tgt, u4 * a->nvbox, st));
         CHK(ensure(t, a->goffd, sizeof(int64_t) * (ngrp + 1), st));
@@ -1043,7 +1063,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
 fmm_status run_adaptive(fmm_tree *t, const Work &w, const void *charges, bool adjoint, bool do_far, bool do_near,
                         hipStream_t st, const Combine *fuse = nullptr, bool *fused = nullptr) {
     const AdTree *a = t->ad;
-    const int P = t->cfg.p, S = coef_stride(P);
+    const int P = t->cfg.p;
     const Ops *o = t->ops;
     t->cur = (int)(t->ncalls % kTimeRing);
     if (t->xyz64.cap < sizeof(double4) * (size_t)t->n || a->lbox.cap < sizeof(int) * (size_t)a->nleaf)
@@ -1083,12 +1103,11 @@ fmm_status run_adaptive(fmm_tree *t, const Work &w, const void *charges, bool ad
     }
     CHK(rec(t, 1, st));
     if (far) {
-        if (!o || !w.farf || !w.M[0] || !w.Lc[0] || w.m2lpart_bytes < ad_m2l_partial_bytes(a->plan, P))
+        if (!o || !w.farf || !w.M[0] || !w.Lc[0] || w.m2lpart_bytes < (f32 ? ad_m2l_partial_bytes(a->plan, P) : fold_partial_bytes(a->fold, P)))
             return fail(FMM_EDEVICE, "internal: no far-field buffers");
         double *M = (double *)w.M[0], *Lc = (double *)w.Lc[0];
         const bool half = m2l_half(t->cfg);
-        if (half && (!w.pack[0] || !w.lmax)) return fail(FMM_EDEVICE, "internal: no binary16 operand buffers");
-        HIPCHK(launch_zero((uint32_t *)(M + (size_t)a->nbox * S), 2 * S, st));  // the zero row
+        if (!w.pack[0] || (half && !w.lmax)) return fail(FMM_EDEVICE, "internal: no M2L operand buffers");
         const int adj = adjoint ? 1 : 0;
         const uint8_t *llev = bp<uint8_t>(a->llev);
         HIPCHK(ad_launch_p2m(P, a->nleaf, lbox, lstart, llev, adj, recs, M, f32, st));
@@ -1108,8 +1127,8 @@ fmm_status run_adaptive(fmm_tree *t, const Work &w, const void *charges, bool ad
                                    bp<int>(a->vidx), a->off[2], bp<int>(a->tgt), a->nbox, w.lmax,
                                    adjoint ? o->aoscale : o->oscale, Lc, w.m2lpart, st));
         else
-            HIPCHK(ad_launch_m2l(P, a->plan, adjoint ? o->am2l64 : o->m2l64, o->cls, M, bp<int>(a->vidx), a->off[2],
-                                 bp<int>(a->tgt), a->nbox, Lc, w.m2lpart, st));
+            HIPCHK(ad_launch_m2l_fold(P, a->fold, adjoint ? o->afold64 : o->fold64, o->fold, M, bp<int>(a->vidx), code,
+                                      a->off[2], a->nbox, Lc, (double *)w.pack[0], w.m2lpart, st));
         CHK(rec(t, 5, st));
         for (int l = 3; l <= a->depth; ++l)
             HIPCHK(ad_launch_l2l(P, a->off[l], a->off[l + 1] - a->off[l], code, bp<int>(a->parent),

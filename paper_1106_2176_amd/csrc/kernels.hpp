@@ -173,7 +173,7 @@ struct AdM2LPlan {
     int64_t units;   // tiles of 128 targets over all groups
     AdM2LGroup grp[kAdMaxGroups];
 };
-// bytes of the K-split partial sums of a plan
+// bytes of the K-split partial sums of a plan (mixed form)
 inline size_t ad_m2l_partial_bytes(const AdM2LPlan &pl, int P) {
     return pl.nsplit > 1 ? sizeof(double) * (size_t)pl.nsplit * pl.units * 128 * P * P : 0;
 }
@@ -196,11 +196,6 @@ hipError_t ad_launch_pack_h(int P, int64_t box2, int64_t nbox, const int *lev, c
 hipError_t ad_launch_m2l_h(int P, const AdM2LPlan &pl, const uint16_t *Ah, size_t astride, const int2 *cls,
                            const void *Bh, const int *vidx, int64_t box2, const int *tgt, int64_t zero_row,
                            const uint32_t *lmax, const float *oscale, double *Lc, double *partial, hipStream_t st);
-// adds M2L over the V slots into Lc; with pl.nsplit > 1 through `partial`
-// (ad_m2l_partial_bytes) and a summing kernel, in a fixed order
-hipError_t ad_launch_m2l(int P, const AdM2LPlan &pl, const double *A, const int2 *cls, const double *M,
-                         const int *vidx, int64_t box2, const int *tgt, int64_t zero_row, double *Lc, double *partial,
-                         hipStream_t st);
 hipError_t ad_launch_p2l(int P, int64_t nbox, const uint32_t *ox, const int *ix, const int *lev,
                          const uint32_t *code, const uint32_t *ps, const uint32_t *pe, int adj, const double4 *rec,
                          double *Lc, bool f32, hipStream_t st);
@@ -253,6 +248,9 @@ struct FoldPlan {
     const double *B[kFoldMaxLev];  // padded operand grid of the level, in K order
     double *L[kFoldMaxLev];
 };
+FoldPlan fold_plan(int P, int64_t tiles, int ncu, size_t cap);
+int fold_tile_targets(int P);
+size_t fold_partial_bytes(const FoldPlan &pl, int P);
 size_t m2l_fold_partial_bytes(int P, int L, int ncu, size_t cap);
 // host tables of order P: K order, its parities in pairs, row order, the
 // orbits (2 bits a component) and room for one operator table, filled at
@@ -261,7 +259,7 @@ struct FoldHost {
     std::vector<int16_t> kperm, rows;
     std::vector<uint16_t> kap;
     std::vector<uint32_t> orbits;
-    std::vector<int2> row_place;
+    std::vector<int2> row_place, cls;
     std::vector<double> table;
 };
 void fold_host(int P, FoldHost &h);
@@ -271,12 +269,20 @@ struct FoldDev {
     const uint32_t *orbits;
     const uint16_t *kap;
     const int16_t *rows, *kperm;
+    const int2 *cls;  // [8][189] (packed source offset, 0): the slots of a class in fold order
 };
 // FP64 multipoles of every level into its padded operand grid, in K order
 hipError_t launch_fold_pack(int P, const PackPlan &pl, const FoldDev &fd, hipStream_t st);
 // every level 2..L in one launch; B[l], Lc[l] indexed by level
 hipError_t launch_m2l_fold(int P, int L, void *const *B, void *const *Lc, const double *A, const FoldDev &fd,
                            double *partial, size_t partial_bytes, int ncu, size_t cap, hipStream_t st);
+
+// m2l_fold_ad.hip: adds the adaptive tree's FP64 M2L over the V slots (in
+// fold order) into Lc; pack: nbox + 1 rows for the multipoles in K order,
+// partial: fold_partial_bytes() of the plan
+hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const FoldDev &fd, const double *M,
+                              const int *vidx, const uint32_t *code, int64_t box2, int64_t nbox, double *Lc,
+                              double *pack, double *partial, hipStream_t st);
 
 // m2l.hip, mixed form: every level 2..L in one launch; B[l], Lc[l] indexed
 // by level.  A = bf16 operator parts spaced astride elements apart (layout

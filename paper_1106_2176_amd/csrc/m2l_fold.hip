@@ -1,61 +1,9 @@
 // m2l_fold.hip -- the FP64 form's multipole-to-local translation on the
-// matrix cores, its offsets folded by reflections (fold.hpp).
-//
-// A target box receives L = sum over the 56 orbits of its offsets of
-// F_d W, where W, for the rows of each of the eight parities, is the sum of
-// the orbit's sources with signs: the rows of parity rho take
-// W_rho[c] = sum_m (-1)^(|rho & m| + |kappa_c & m|) M_m[c] over the pair
-// masks m of the orbit, kappa_c the parity of coefficient c.  With the
-// sources' signs (-1)^|kappa_c & m| put on first, that is a Walsh-Hadamard
-// transform in up to three butterfly stages.  A target of class k sees its
-// offsets reflected in the axes of k, which is one more sign per
-// coefficient, |kappa_c & k|, and one per row, |rho & k|; the operators are
-// those of class 0, so that targets of every class and level share them and
-// are taken in one list, 16 to a wave.
-//
-// What bounds it: the FP64 matrix cores.  While an FP64 matrix product runs
-// its SIMD issues no vector instruction (8 products and 48 FMAs took the sum
-// of their times, in one wave and in two), so the butterflies, the signs and
-// the address arithmetic add to it.  Direct products over the 189 offsets
-// (v_mfma_f64_16x16x4_f64, 112 rows) took 2.2e6 matrix cycles per 16 targets
-// at p = 10; folded they take 0.52e6: 56 products in place of 189, those of
-// an orbit with a zero axis halved, and rows padded to 4 within a parity.
-// Rows in fours use v_mfma_f64_4x4x4_f64, whose four blocks take the same
-// operator rows and four columns each, at the same 32 FLOP per cycle and
-// SIMD as the 16 x 16 x 4 instruction (75 and 78 TFLOP/s measured), and
-// groups of four quads of a parity the latter, which reads a quarter of the
-// operators from LDS.
-// Measured, N = 1e6 uniform particles at p = 10 (32768 leaves): 0.99 ms, the
-// direct kernel 3.83 ms; at p = 12, 4096 leaves: 0.27 against 1.25 ms; at
-// p = 8, 4096 leaves: 0.085 against 0.25 ms.
-// Lane layouts (measured on gfx950), 4 x 4 x 4: A lane l holds row l % 4 of
-// K index l / 16 (the same for the four blocks), B lane l column l % 16 of
-// K index l / 16, the result lane l row l / 16 of column l % 16; 16 x 16 x 4:
-// A lane l row l % 16 of K index l / 16, B alike, the result's item i in
-// lane l row l / 16 + 4 i.
-#include "fold.hpp"
-#include "kernels.hpp"
+// matrix cores, its offsets folded by reflections (fold.hpp, fold_kernel.hpp):
+// the uniform tree's kernels and the tables' host side.
+#include "fold_kernel.hpp"
 
 namespace fmm {
-
-namespace {
-
-// A block is a tile of 16 targets per wave: eight waves (two per SIMD) up to
-// p = 12, where the accumulators (one double per row quad), the transformed
-// sources and the sources a chunk ahead fit 256 registers; four waves (one
-// per SIMD, 512 registers) above, where they would spill.  The operators of
-// a chunk (8 K positions) pass through LDS, double buffered, for all waves.
-__host__ __device__ constexpr int fold_waves(int P) { return P <= 12 ? 8 : 4; }
-__host__ __device__ constexpr int fold_tile(int P) { return 16 * fold_waves(P); }
-
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ double flip(double v, uint32_t sign) {
-    uint64_t u = __builtin_bit_cast(uint64_t, v);
-    u ^= (uint64_t)sign << 32;
-    return __builtin_bit_cast(double, u);
-}
 
 // The sources of a tile: the children of its parents (4 x 2 x 2 of them, 2 x
 // 2 x 2 in a four-wave tile) and of their neighbours, 12 x 8 x 8 boxes.  The
@@ -66,7 +14,56 @@ __device__ __forceinline__ double flip(double v, uint32_t sign) {
 // targets (5.2 GB at p = 10, 32768 boxes: the kernel took 1.45 ms).
 constexpr int kRegY = 12, kRegZ = 104, kRegPlane = 8 * kRegZ;
 
-}  // namespace
+template <int P>
+struct GridSource {
+    static constexpr int S = coef_stride(P), NT = 64 * fold_waves(P);
+    static constexpr int RX = fold_waves(P) == 8 ? 12 : 8;  // region boxes along x
+    static constexpr int REG = RX * 8 * 8 * 4 / NT;         // region pieces per thread
+    static_assert(RX * 8 * 8 * 4 % NT == 0, "region pieces");
+    const double *__restrict__ B;  // the level's padded grid
+    int G, ox, oy, oz;             // its pitch, the tile's origin
+    f64x2 *reg;
+    int here, st[3];               // the lane's target in the region, strides signed by its class
+    int d[3];
+    __device__ __forceinline__ void chunk(int j) {
+        // boxes past the grid's halo (a tile wider than its level) read the halo
+        f64x2 v[REG];
+#pragma unroll
+        for (int i = 0; i < REG; ++i) {
+            const int e = threadIdx.x + NT * i, bx = e >> 2, rx = bx % RX, ry = bx / RX % 8, rz = bx / (RX * 8);
+            const int64_t at = (int64_t)min(ox + rx + 1, G - 1) +
+                               G * ((int64_t)min(oy + ry + 1, G - 1) + (int64_t)G * min(oz + rz + 1, G - 1));
+            v[i] = *(const f64x2 *)(B + at * S + 8 * j + 2 * (e & 3));
+        }
+#pragma unroll
+        for (int i = 0; i < REG; ++i) {
+            const int e = threadIdx.x + NT * i, bx = e >> 2, rx = bx % RX, ry = bx / RX % 8, rz = bx / (RX * 8);
+            reg[(e & 3) * kRegPlane + rx + kRegY * ry + kRegZ * rz] = v[i];
+        }
+    }
+    template <int T>
+    __device__ __forceinline__ void fetch(int, uint32_t e) {
+        d[0] = __mul24((int)(e & 3), st[0]);
+        d[1] = __mul24((int)((e >> 2) & 3), st[1]);
+        d[2] = __mul24((int)((e >> 4) & 3), st[2]);
+    }
+    template <int T, int HALF>
+    __device__ __forceinline__ void load(int sw, double (&nx)[8][2]) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+            if ((m & ~T) == 0) {
+                const int at = here + (m & 1 ? -d[0] : d[0]) + (m & 2 ? -d[1] : d[1]) + (m & 4 ? -d[2] : d[2]);
+                if (HALF) {
+                    nx[m][0] = ((const double *)(reg + at))[sw];
+                    nx[m][1] = ((const double *)(reg + at))[1 - sw];
+                } else {
+                    const f64x2 v = reg[at];
+                    nx[m][0] = v.x;
+                    nx[m][1] = v.y;
+                }
+            }
+    }
+};
 
 // Tile of the flat list: its level's index, the level, its first target
 // (Morton) and its column's target
@@ -108,240 +105,39 @@ __global__ __launch_bounds__(256) void k_fold_pack(int P, PackPlan pl, const int
 template <int P>
 __global__ __launch_bounds__(64 * fold_waves(P))
 __attribute__((amdgpu_waves_per_eu(fold_waves(P) / 4, fold_waves(P) / 4))) void k_m2l_fold(
-    FoldPlan pl, const double *__restrict__ A, const uint32_t *__restrict__ orbits, const uint16_t *__restrict__ kap, const int16_t *__restrict__ rows,
-    double *__restrict__ partial) {
-    constexpr FoldTab<P> F = fold_tab<P>();
-    constexpr FoldOrbits O = fold_orbits();
-    constexpr int P2 = P * P, S = coef_stride(P), RQ = fold_row_quads(P), NCH = FoldTab<P>::NCH;
-    constexpr int NT = 64 * fold_waves(P);
-    // a step's operators: NPC 16-byte pieces, fetched by the waves of one of
-    // four groups
-    constexpr int NPC = RQ * 16, GT = NT / 4, EPT = (NPC + GT - 1) / GT;
-    constexpr int RX = fold_waves(P) == 8 ? 12 : 8;          // region boxes along x
-    constexpr int REG = RX * 8 * 8 * 4 / NT;                 // region pieces per thread
-    static_assert(RX * 8 * 8 * 4 % NT == 0, "region pieces");
-    __shared__ __align__(16) f64x2 As[4 * NPC];
+    FoldPlan pl, const double *__restrict__ A, const uint32_t *__restrict__ orbits, const uint16_t *__restrict__ kap,
+    const int16_t *__restrict__ rows, double *__restrict__ partial) {
+    constexpr int P2 = P * P, S = coef_stride(P);
+    __shared__ __align__(16) f64x2 As[4 * kFoldPieces<P>];
     __shared__ __align__(16) f64x2 reg[4 * kRegPlane];
-
-    // block -> tile and its range of steps (chunk, orbit): whole tiles first,
-    // each XCD a contiguous run of them, then the parts of the rest
-    const int64_t b = blockIdx.x;
     int64_t tile;
-    int part = -1, sbeg = 0, send = NCH * kFoldOrbits;
-    if (b < pl.nfull) {
-        const int64_t per = pl.nfull >> 3;
-        tile = b < 8 * per ? (b & 7) * per + (b >> 3) : b;
-    } else {
-        const int64_t r = b - pl.nfull;
-        part = (int)(r / pl.nrest);
-        tile = pl.nfull + (r - (int64_t)part * pl.nrest);
-        sbeg = pl.cut[part];
-        send = pl.cut[part + 1];
-    }
+    int part, sbeg, send;
+    fold_unit(pl, coef_stride(P) / 8, tile, part, sbeg, send);
     int li, l;
     int64_t m0;
     fold_place_of(pl, tile, li, l, m0);
-    const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, slot = (tid >> 6) * 16 + (lane & 15);
-    const int n = 1 << l, G = n + 6;
-    const int64_t m = m0 + slot;
-    const bool valid = m < ((int64_t)1 << (3 * l));
-    const int k = slot & 7;
-    // tile origin, and this lane's place in the region
-    const int ox = (int)compact3((uint32_t)m0), oy = (int)compact3((uint32_t)m0 >> 1), oz = (int)compact3((uint32_t)m0 >> 2);
+    const int lane = threadIdx.x & 63, q = lane >> 4, slot = (threadIdx.x >> 6) * 16 + (lane & 15), k = slot & 7;
+    const int n = 1 << l;
     const int x = (int)compact3((uint32_t)slot), y = (int)compact3((uint32_t)slot >> 1), z = (int)compact3((uint32_t)slot >> 2);
-    const int here = (x + 2) + kRegY * (y + 2) + kRegZ * (z + 2) + q * kRegPlane;
-    const int st[3] = {k & 1 ? -1 : 1, k & 2 ? -kRegY : kRegY, k & 4 ? -kRegZ : kRegZ};
-    // region pieces of this thread: box e / 4, pair e % 4; boxes past the
-    // grid's halo (a tile wider than its level) read the halo
-    const double *__restrict__ B = pick(pl.B, li);
-    int64_t gsrc[REG];
-    int gdst[REG];
-#pragma unroll
-    for (int i = 0; i < REG; ++i) {
-        const int e = tid + NT * i, bx = e >> 2, rx = bx % RX, ry = bx / RX % 8, rz = bx / (RX * 8);
-        gsrc[i] = ((int64_t)min(ox + rx + 1, G - 1) + G * ((int64_t)min(oy + ry + 1, G - 1) +
-                                                          (int64_t)G * min(oz + rz + 1, G - 1))) * S + 2 * (e & 3);
-        gdst[i] = (e & 3) * kRegPlane + rx + kRegY * ry + kRegZ * rz;
-    }
-    // sums of the lane's rows q of each row quad: of four quads in one
-    // accumulator of the 16 x 16 instruction, and of the single ones
-    constexpr int NBIG = fold_bigs(P, 8);
-    f64x4 big[NBIG + 1];
-    double one[RQ - 4 * NBIG + 1];
-#pragma unroll
-    for (int r = 0; r < NBIG; ++r) big[r] = f64x4{0, 0, 0, 0};
-#pragma unroll
-    for (int r = 0; r < RQ - 4 * NBIG; ++r) one[r] = 0.0;
-
-    // The operators are one stream for every block, which each XCD's L2 misses
-    // on the way: each of four groups of waves fetches every fourth step's,
-    // and stores them a pair of steps ahead, so that a barrier every second
-    // step is enough (the two waves of a SIMD then drift apart and one's
-    // transform runs beside the other's products).
-    const int grp = __builtin_amdgcn_readfirstlane(tid >> 6) & 3;
-    const int gt = (tid >> 8) * 64 + lane;  // thread within its group
-    f64x2 ar[EPT];
-    auto load_a = [&](int s) __attribute__((always_inline)) {
-        const f64x2 *a = (const f64x2 *)A + (size_t)min(s, send - 1) * NPC;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) ar[i] = a[min(gt + GT * i, NPC - 1)];
-    };
-    auto store_a = [&](int s) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = gt + GT * i;
-            if (NPC % GT == 0 || e < NPC) As[(s & 3) * NPC + e] = ar[i];
-        }
-    };
-    int step = sbeg;
-    const int pair0 = sbeg & ~1;
-    int fetched = pair0 + ((grp - pair0) & 3);  // the step whose operators are in ar
-    load_a(fetched);
-    if (fetched < pair0 + 2) {
-        store_a(fetched);
-        load_a(fetched += 4);
-    }
-    for (int j = sbeg / kFoldOrbits; j * kFoldOrbits < send; ++j) {
-        // the chunk's region (every wave is past the last one's)
-        {
-            f64x2 v[REG];
-#pragma unroll
-            for (int i = 0; i < REG; ++i) v[i] = *(const f64x2 *)(B + gsrc[i] + 8 * j);
-#pragma unroll
-            for (int i = 0; i < REG; ++i) reg[gdst[i]] = v[i];
-        }
-        lds_barrier();
-        const int obeg = max(sbeg - j * kFoldOrbits, 0), oend = min(send - j * kFoldOrbits, kFoldOrbits);
-        const uint32_t kk = kap[4 * j + q];  // parities of the lane's two positions
-        const bool paired = j < F.npair;
-        // The orbits [o0, o1) of pair mask T.  HALF = 0: every row with both
-        // positions of each pair; HALF = 1 + axis (opposite pairs, zero
-        // axis): element 0 is the one that is even along the axis, which the
-        // even rows meet, element 1 the odd one.
-        auto orbit_loop = [&](auto Tc, auto Hc, int o0, int o1) __attribute__((always_inline)) {
-            constexpr int T = decltype(Tc)::value, HALF = decltype(Hc)::value;
-            if (o0 >= o1) return;
-            const int sw = HALF ? (int)((kk >> (HALF ? HALF - 1 : 0)) & 1) : 0;  // the lane's elements swapped
-            uint32_t sg[2][4];  // signs of the elements: class, then each axis
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const uint32_t kp = (kk >> (8 * (e ^ sw))) & 7;
-                sg[e][0] = (uint32_t)__popc(kp & (uint32_t)k) << 31;
-                sg[e][1] = kp << 31;
-                sg[e][2] = (kp >> 1) << 31;
-                sg[e][3] = (kp >> 2) << 31;
-            }
-            const double *const r0 = (const double *)(reg + here) + sw, *const r1 = (const double *)(reg + here) + (1 - sw);
-            double nx[8][2], w[8][2];
-            auto load_b = [&](uint32_t e) __attribute__((always_inline)) {
-                const int d0 = __mul24((int)(e & 3), st[0]), d1 = __mul24((int)((e >> 2) & 3), st[1]),
-                          d2 = __mul24((int)((e >> 4) & 3), st[2]);
-#pragma unroll
-                for (int mm = 0; mm < 8; ++mm)
-                    if ((mm & ~T) == 0) {
-                        const int at = (mm & 1 ? -d0 : d0) + (mm & 2 ? -d1 : d1) + (mm & 4 ? -d2 : d2);
-                        if (HALF) {
-                            nx[mm][0] = r0[2 * at];
-                            nx[mm][1] = r1[2 * at];
-                        } else {
-                            const f64x2 v = reg[here + at];
-                            nx[mm][0] = v.x;
-                            nx[mm][1] = v.y;
-                        }
-                    }
-            };
-            load_b(orbits[o0]);
-            uint32_t en = orbits[min(o0 + 1, o1 - 1)];  // the next orbit
-            for (int o = o0; o < o1; ++o, ++step) {
-                // the next pair of steps' operators into the buffers that
-                // every wave finished reading before the last barrier
-                if ((!(step & 1) || step == sbeg) && fetched < (step & ~1) + 4) {
-                    store_a(fetched);
-                    load_a(fetched += 4);
-                }
-                // transform of the sources
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-#pragma unroll
-                    for (int mm = 0; mm < 8; ++mm)
-                        if ((mm & ~T) == 0)
-                            w[mm][e] = flip(nx[mm][e], sg[e][0] ^ (mm & 1 ? sg[e][1] : 0u) ^ (mm & 2 ? sg[e][2] : 0u) ^
-                                                           (mm & 4 ? sg[e][3] : 0u));
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) {
-                        const int bit = 1 << d;
-                        if (!(T & bit)) continue;
-#pragma unroll
-                        for (int mm = 0; mm < 8; ++mm)
-                            if ((mm & ~T) == 0 && !(mm & bit)) {
-                                const double u = w[mm][e], v = w[mm | bit][e];
-                                w[mm][e] = u + v;
-                                w[mm | bit][e] = u - v;
-                            }
-                    }
-                }
-                load_b(en);
-                en = orbits[min(o + 2, o1 - 1)];
-                // products: four row quads of a parity at a time, then the
-                // single ones
-                const f64x2 *ab = As + (step & 3) * NPC + lane, *as = As + (step & 3) * NPC + (q * 4 + (lane & 3));
-                static_for<0, 8>([&](auto rc) __attribute__((always_inline)) {
-                    constexpr int rho = decltype(rc)::value, R0 = F.rq0[rho], NR = F.rq0[rho + 1] - R0;
-                    constexpr int NB = NR / 4, N1 = NR - 4 * NB, B0 = fold_bigs(P, rho), R1 = R0 + 4 * NB;
-                    constexpr int e = HALF ? (rho >> (HALF ? HALF - 1 : 0)) & 1 : 0;
-                    const int off = e ? 1 - sw : sw;
-                    f64x2 g[NB + 1], a[N1 + 1];
-#pragma unroll
-                    for (int r = 0; r < NB; ++r) {
-                        if (HALF) g[r].x = ((const double *)(ab + 16 * (R0 + 4 * r)))[off];
-                        else g[r] = ab[16 * (R0 + 4 * r)];
-                    }
-#pragma unroll
-                    for (int r = 0; r < N1; ++r) {
-                        if (HALF) a[r].x = ((const double *)(as + 16 * (R1 + r)))[off];
-                        else a[r] = as[16 * (R1 + r)];
-                    }
-#pragma unroll
-                    for (int h = 0; h < (HALF ? 1 : 2); ++h) {
-                        const double v = w[rho & T][HALF ? e : h];
-#pragma unroll
-                        for (int r = 0; r < NB; ++r)
-                            big[B0 + r] = __builtin_amdgcn_mfma_f64_16x16x4f64(h ? g[r].y : g[r].x, v, big[B0 + r], 0, 0, 0);
-#pragma unroll
-                        for (int r = 0; r < N1; ++r)
-                            one[R1 - 4 * (B0 + NB) + r] = __builtin_amdgcn_mfma_f64_4x4x4f64(
-                                h ? a[r].y : a[r].x, v, one[R1 - 4 * (B0 + NB) + r], 0, 0, 0);
-                    }
-                });
-                if (step & 1) lds_barrier();
-            }
-        };
-        static_for<0, 8>([&](auto Tc) __attribute__((always_inline)) {
-            constexpr int T = decltype(Tc)::value;
-            // without a zero axis, or all of them where pairs are not opposite
-            orbit_loop(Tc, std::integral_constant<int, 0>{}, max(obeg, O.t0[T][0]), min(oend, O.t0[T][paired ? 1 : 4]));
-            if (paired)
-                static_for<1, 4>([&](auto Hc) __attribute__((always_inline)) {
-                    constexpr int H = decltype(Hc)::value;
-                    if constexpr (O.t0[T][H + 1] > O.t0[T][H])
-                        orbit_loop(Tc, Hc, max(obeg, O.t0[T][H]), min(oend, O.t0[T][H + 1]));
-                });
-        });
-    }
-    double *dst = part < 0
-                      ? pick(pl.L, li) + ((int64_t)(ox + x) + (int64_t)n * ((oy + y) + (int64_t)n * (oz + z))) * S
-                      : partial + (((int64_t)part * pl.nrest + (tile - pl.nfull)) * (NT / 4) + slot) * P2;
-    static_for<0, 8>([&](auto rc) __attribute__((always_inline)) {
-        constexpr int rho = decltype(rc)::value, R0 = F.rq0[rho], NR = F.rq0[rho + 1] - R0;
-        constexpr int NB = NR / 4, B0 = fold_bigs(P, rho);
-        const uint32_t sign = (uint32_t)__popc(rho & k) << 31;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int c = rows[4 * (R0 + r) + q];
-            const double v = r < 4 * NB ? big[B0 + r / 4][r % 4] : one[R0 + r - 4 * (B0 + NB)];
-            if (valid && c >= 0) dst[c] = flip(v, sign);
-        }
-    });
+    GridSource<P> src;
+    src.B = pick(pl.B, li);
+    src.G = n + 6;
+    src.ox = (int)compact3((uint32_t)m0);
+    src.oy = (int)compact3((uint32_t)m0 >> 1);
+    src.oz = (int)compact3((uint32_t)m0 >> 2);
+    src.reg = reg;
+    src.here = (x + 2) + kRegY * (y + 2) + kRegZ * (z + 2) + q * kRegPlane;
+    src.st[0] = k & 1 ? -1 : 1;
+    src.st[1] = k & 2 ? -kRegY : kRegY;
+    src.st[2] = k & 4 ? -kRegZ : kRegZ;
+    FoldAcc<P> acc;
+    acc.clear();
+    fold_run<P>(src, k, sbeg, send, A, orbits, kap, As, acc);
+    if (m0 + slot >= (int64_t)1 << (3 * l)) return;
+    double *dst = part < 0 ? pick(pl.L, li) + ((int64_t)(src.ox + x) +
+                                               (int64_t)n * ((src.oy + y) + (int64_t)n * (src.oz + z))) * S
+                           : partial + (((int64_t)part * pl.nrest + (tile - pl.nfull)) * fold_tile(P) + slot) * P2;
+    acc.each(k, q, rows, [&](int c, double v) __attribute__((always_inline)) { dst[c] = v; });
 }
 
 // Sum of the parts of the rest tiles, in part order; one thread per target
@@ -365,20 +161,15 @@ __global__ __launch_bounds__(256) void k_m2l_fold_sum(int P, FoldPlan pl, const 
 }
 
 // ------------------------------------------------------------ host side
+int fold_tile_targets(int P) { return fold_tile(P); }
+
 // Tiles to compute units: as many whole rounds of one tile per unit as there
 // are, then the rest in s parts of their steps, s the count that takes the
 // least time among those whose FP64 partial sums fit `cap` bytes.
-static FoldPlan fold_plan(int P, int L, int ncu, size_t cap) {
+FoldPlan fold_plan(int P, int64_t tiles, int ncu, size_t cap) {
     constexpr FoldOrbits O = fold_orbits();
     FoldPlan pl{};
     pl.tile = fold_tile(P);
-    pl.nlev = L - 1;
-    int64_t tiles = 0;
-    for (int i = 0; i < pl.nlev; ++i) {
-        pl.level[i] = L - i;
-        pl.tile0[i] = tiles;
-        tiles += (((int64_t)1 << (3 * (L - i))) + pl.tile - 1) / pl.tile;
-    }
     pl.nfull = tiles / ncu * ncu;
     pl.nrest = (int)(tiles - pl.nfull);
     pl.nsplit = 1;
@@ -414,12 +205,28 @@ static FoldPlan fold_plan(int P, int L, int ncu, size_t cap) {
     return pl;
 }
 
-static size_t plan_partial_bytes(const FoldPlan &pl, int P) {
+// the uniform tree's tiles, the largest level first
+static FoldPlan grid_plan(int P, int L, int ncu, size_t cap) {
+    int64_t tiles = 0, tile0[kFoldMaxLev] = {};
+    for (int i = 0; i < L - 1; ++i) {
+        tile0[i] = tiles;
+        tiles += (((int64_t)1 << (3 * (L - i))) + fold_tile(P) - 1) / fold_tile(P);
+    }
+    FoldPlan pl = fold_plan(P, tiles, ncu, cap);
+    pl.nlev = L - 1;
+    for (int i = 0; i < L - 1; ++i) {
+        pl.level[i] = L - i;
+        pl.tile0[i] = tile0[i];
+    }
+    return pl;
+}
+
+size_t fold_partial_bytes(const FoldPlan &pl, int P) {
     return pl.nrest ? sizeof(double) * (size_t)pl.nsplit * pl.nrest * pl.tile * P * P : 0;
 }
 
 size_t m2l_fold_partial_bytes(int P, int L, int ncu, size_t cap) {
-    return L < 2 ? 0 : plan_partial_bytes(fold_plan(P, L, ncu, cap), P);
+    return L < 2 ? 0 : fold_partial_bytes(grid_plan(P, L, ncu, cap), P);
 }
 
 template <int P>
@@ -456,6 +263,16 @@ void fold_host(int P, FoldHost &h) {
     h.orbits.clear();
     for (int o = 0; o < kFoldOrbits; ++o)
         h.orbits.push_back(O.o[o].a[0] | O.o[o].a[1] << 2 | O.o[o].a[2] << 4);
+    // slots of each class: its offsets are class 0's with the axes of k negated
+    h.cls.assign((size_t)8 * kOffsetsPerClass, int2{0, 0});
+    for (int k = 0; k < 8; ++k)
+        for (int o = 0; o < kFoldOrbits; ++o)
+            for (int m = 0; m < 8; ++m) {
+                if (m & ~O.o[o].T) continue;
+                int d[3];
+                for (int a = 0; a < 3; ++a) d[a] = (((m ^ k) >> a) & 1 ? -O.o[o].a[a] : O.o[o].a[a]) + 4;
+                h.cls[(size_t)k * kOffsetsPerClass + O.src0[o] + fold_rank(O.o[o].T, m)].x = d[0] | d[1] << 4 | d[2] << 8;
+            }
     h.table.assign(fold_table_size(P), 0.0);
 }
 
@@ -474,8 +291,8 @@ hipError_t launch_fold_pack(int P, const PackPlan &pl, const FoldDev &fd, hipStr
 hipError_t launch_m2l_fold(int P, int L, void *const *B, void *const *Lc, const double *A, const FoldDev &fd,
                            double *partial, size_t partial_bytes, int ncu, size_t cap, hipStream_t st) {
     if (L < 2) return hipSuccess;
-    FoldPlan pl = fold_plan(P, L, ncu, cap);
-    if (plan_partial_bytes(pl, P) > 0 && (!partial || partial_bytes < plan_partial_bytes(pl, P)))
+    FoldPlan pl = grid_plan(P, L, ncu, cap);
+    if (fold_partial_bytes(pl, P) > 0 && (!partial || partial_bytes < fold_partial_bytes(pl, P)))
         return hipErrorInvalidValue;
     for (int i = 0; i < pl.nlev; ++i) {
         pl.B[i] = (const double *)B[pl.level[i]];

@@ -42,3 +42,22 @@ def test_far_field_and_adjoint_match_the_oracle(oracle_mod, p, n, leaf, level):
     gq_o, gx_o, _ = oracle_mod.fmm_grad(pos, q, w, p, leaf)
     assert rel_l2(gq.cpu().numpy(), gq_o) < 1e-10
     assert rel_l2(gx.cpu().numpy(), gx_o) < 1e-10
+
+
+@pytest.mark.parametrize("p,leaf", [(2, 8), (8, 32)])
+def test_adaptive_noalloc_matches_evaluate(p, leaf):
+    """The scratch form puts the adaptive tree's operands over the near and
+    far partials (or beside them, where they do not fit): bitwise the same."""
+    import ctypes
+    pos, q = inputs.clustered(20_000, 310 + p)
+    Q = dev(q)
+    with fmm.Tree(dev(pos), p=p, leaf_max=leaf, precision="fp64", adaptive=True) as t:
+        for part, flags in ((None, fmm.VEC_FIELD), ("far", fmm.VEC_FIELD | fmm.PART_FAR_ONLY)):
+            phi, E = t.evaluate(Q, part=part)
+            phi2, E2 = torch.full_like(phi, float("nan")), torch.full_like(E, float("nan"))
+            rc = fmm.lib().fmm_evaluate_noalloc(t._h, ctypes.c_void_p(Q.data_ptr()), ctypes.c_void_p(phi2.data_ptr()),
+                                                ctypes.c_void_p(E2.data_ptr()), flags,
+                                                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+            torch.cuda.synchronize()
+            assert rc == fmm.FMM_OK
+            assert torch.equal(phi, phi2) and torch.equal(E, E2)
