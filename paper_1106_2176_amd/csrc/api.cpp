@@ -3,6 +3,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <new>
@@ -56,7 +57,61 @@ void ensure_pool(int dev) {
 struct Buf {
     void *p = nullptr;
     size_t cap = 0;
+    bool part = false;  // lies in another buffer (place())
 };
+
+// Pinned words for a build's counts and the event behind them.  Allocating
+// and freeing pinned memory costs more than the rest of a small tree's life
+// (the free waits for the device), so a destroyed tree leaves its kit for the
+// next one on its device; at most kKits wait, the others are freed.
+constexpr int kAdHostWords = 128;  // adaptive build: 4 totals + 8 groups per level 2..10
+struct HostKit {
+    int dev = 0;
+    unsigned int *words = nullptr;      // pinned, coherent: 4 counters, then kAdHostWords
+    unsigned int *words_dev = nullptr;  // their address for kernels
+    hipEvent_t ev = nullptr;            // after the copy of the build counters
+};
+constexpr size_t kKits = 8;
+std::mutex g_kit_mu;
+std::vector<HostKit> g_kits;
+
+void kit_free(HostKit &k) {
+    if (k.ev) (void)hipEventDestroy(k.ev);
+    if (k.words) (void)hipHostFree(k.words);
+    k = HostKit{};
+}
+
+hipError_t kit_get(int dev, HostKit &k) {
+    {
+        std::lock_guard<std::mutex> g(g_kit_mu);
+        for (size_t i = 0; i < g_kits.size(); ++i)
+            if (g_kits[i].dev == dev) {
+                k = g_kits[i];
+                g_kits.erase(g_kits.begin() + (long)i);
+                return hipSuccess;
+            }
+    }
+    k.dev = dev;
+    hipError_t e = hipHostMalloc((void **)&k.words, (4 + kAdHostWords) * sizeof(unsigned int), hipHostMallocCoherent);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&k.words_dev, k.words, 0);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&k.ev, hipEventDisableTiming);
+    if (e != hipSuccess) kit_free(k);
+    return e;
+}
+
+// idle: no device work that writes the words is pending
+void kit_put(HostKit &k, bool idle) {
+    if (!k.words) return;
+    if (idle) {
+        std::lock_guard<std::mutex> g(g_kit_mu);
+        if (g_kits.size() < kKits) {
+            g_kits.push_back(k);
+            k = HostKit{};
+            return;
+        }
+    }
+    kit_free(k);
+}
 
 // ------------------------------------------------------------ operators
 struct Ops {
@@ -368,7 +423,6 @@ struct GraphSlot {
 // concatenated breadth first), the U/W/X lists in CSR form, the V lists as
 // 189 slots per box of level >= 2, the leaves in particle order, and host
 // copies of the level offsets and of the M2L target groups.
-constexpr int kAdHostWords = 128;  // 4 totals + 8 groups per level 2..10
 struct AdTree {
     int depth = 0;
     int64_t nbox = 0, nleaf = 0, nvbox = 0;  // nvbox: boxes of levels >= 2
@@ -377,16 +431,12 @@ struct AdTree {
     int64_t goff[8 * FMM_MAX_LEVEL + 1] = {}; // first target of each (level, class) group
     AdM2LPlan plan{};                         // mixed form
     FoldPlan fold{};                          // FP64 form
-    uint32_t *hbuf = nullptr;                 // pinned host words for the build's counts
+    uint32_t *hbuf = nullptr;                 // the kit's words for the build's counts
     Buf code, ps, pe, parent, child, leaf, cmask, nchild, coff, lev, col, vidx, cnts, offs, iu, iw, ix,
         is_head, head, hoff, lbox, lstart, llev, tgt, ccnt, goffd, offd, ucnt, uoff, units, s27, units_m;
     Buf skey, cstart, ks_a, ks_b, ks_v, ks_h;  // the key sort: sorted keys, coarse starts, scratch
+    Buf area[3];            // hold the buffers above: by particles and box bound, by boxes, by list items
     int64_t max_units = 0;  // bound of the P2P work units (their count stays on the device)
-    std::vector<Buf *> bufs() {
-        return {&code, &ps, &pe, &parent, &child, &leaf, &cmask, &nchild, &coff, &lev, &col, &vidx, &cnts,
-                &offs, &iu, &iw, &ix, &is_head, &head, &hoff, &lbox, &lstart, &llev, &tgt, &ccnt, &goffd,
-                &offd, &ucnt, &uoff, &units, &s27, &skey, &cstart, &ks_a, &ks_b, &ks_v, &ks_h, &units_m};
-    }
 };
 
 }  // namespace
@@ -402,12 +452,13 @@ struct fmm_tree {
     int ncu = 0;  // compute units of the device
     hipStream_t stream = nullptr;
     Alloc al;
-    Buf key10, rank, cnt, start, tmp, perm, scan, counters, xyz32, xyz64, nearf, farf, pairs, m2lpart,
-        lmax;
-    hipEvent_t ev_counters = nullptr;  // after the copy of the build counters
-    Buf M[FMM_MAX_LEVEL + 1], Lc[FMM_MAX_LEVEL + 1], pack[FMM_MAX_LEVEL + 1];
-    unsigned int *host_counters = nullptr;  // pinned [4]
-    unsigned int *host_counters_dev = nullptr;  // their address for kernels
+    Buf key10, rank, cnt, start, tmp, perm, scan, counters, xyz32, xyz64;  // in parts and levels
+    Buf parts, levels;          // build buffers by particles and by leaves
+    Buf work;                   // the per-call buffers (work_buffers)
+    Buf pairs;
+    HostKit kit;
+    bool kit_idle = false;      // the last build has read its counts
+    bool strayed = false;       // used on a stream other than its build's
     Ops *ops = nullptr;
     hipEvent_t ev[kTimeRing][kEvents] = {};
     bool p2p_side[kTimeRing] = {};  // the call's P2P ran on the side stream
@@ -533,6 +584,27 @@ void release(fmm_tree *t, Buf &b, hipStream_t st) {
     b.cap = 0;
 }
 
+// Lay buffers of the given sizes one after another, 256-byte aligned, in
+// `area` (grown through the tree's allocator where it is too small; what it
+// held is then lost).  One allocation in the place of many: each call of the
+// caller's allocator costs microseconds.
+struct Want {
+    Buf *b;
+    size_t bytes;
+};
+fmm_status place(fmm_tree *t, Buf &area, std::initializer_list<Want> want, hipStream_t st) {
+    size_t total = 0;
+    for (const Want &w : want) total += (std::max<size_t>(w.bytes, 1) + 255) & ~(size_t)255;
+    const fmm_status s = ensure(t, area, total, st);
+    if (s != FMM_OK) return s;
+    size_t off = 0;
+    for (const Want &w : want) {
+        *w.b = Buf{(unsigned char *)area.p + off, w.bytes, true};
+        off += (std::max<size_t>(w.bytes, 1) + 255) & ~(size_t)255;
+    }
+    return FMM_OK;
+}
+
 fmm_status validate_cfg(const fmm_config *c) {
     if (!c) return fail(FMM_EINVAL, "config is NULL");
     if (c->abi_version != FMM_ABI_VERSION) return fail(FMM_EINVAL, "ABI version mismatch");
@@ -594,42 +666,11 @@ fmm_status rec(fmm_tree *t, int stage, hipStream_t st) {
         if (s_ != FMM_OK) return s_;     \
     } while (0)
 
-// Per-call buffers from the tree's workspace, grown through its allocator.
-fmm_status work_from_tree(fmm_tree *t, bool far, hipStream_t st, Work &w) {
-    const WorkSizes z = work_sizes(t, far);
-    CHK(ensure(t, t->nearf, z.nearf, st));
-    w.nearf = (double4 *)t->nearf.p;
-    if (!z.farf) return FMM_OK;
-    CHK(ensure(t, t->farf, z.farf, st));
-    w.farf = (double4 *)t->farf.p;
-    for (int l = 0; l <= FMM_MAX_LEVEL; ++l) {
-        if (z.M[l]) {
-            CHK(ensure(t, t->M[l], z.M[l], st));
-            CHK(ensure(t, t->Lc[l], z.Lc[l], st));
-            w.M[l] = t->M[l].p;
-            w.Lc[l] = t->Lc[l].p;
-        }
-        if (z.pack[l]) {
-            CHK(ensure(t, t->pack[l], z.pack[l], st));
-            w.pack[l] = t->pack[l].p;
-        }
-    }
-    if (z.m2lpart) {
-        CHK(ensure(t, t->m2lpart, z.m2lpart, st));
-        w.m2lpart = (double *)t->m2lpart.p;
-        w.m2lpart_bytes = t->m2lpart.cap;
-    }
-    if (z.lmax) {
-        CHK(ensure(t, t->lmax, z.lmax, st));
-        w.lmax = (uint32_t *)t->lmax.p;
-    }
-    return FMM_OK;
-}
-
-// Per-call buffers carved, 256-byte aligned, from the static scratch array
+// Per-call buffers, 256-byte aligned, in one run of memory: the tree's work
+// buffer, grown through its allocator, or (scratch) the static scratch array
 // of the current device (FMM_NOALLOC_SCRATCH_BYTES).  Nothing in them needs
 // clearing: every kernel writes each element before any kernel reads it.
-fmm_status work_from_scratch(fmm_tree *t, bool far, Work &w) {
+fmm_status work_buffers(fmm_tree *t, bool far, bool scratch, hipStream_t st, Work &w) {
     const WorkSizes z = work_sizes(t, far);
     size_t off = 0;
     auto take = [&](size_t bytes) -> size_t {
@@ -645,19 +686,24 @@ fmm_status work_from_scratch(fmm_tree *t, bool far, Work &w) {
             oM[l] = take(z.M[l]);
             oL[l] = take(z.Lc[l]);
         }
-        // the adaptive tree's operands lie over the near and far partials
-        // where they fit: M2L ends before either is written
-        if (t->ad && z.pack[l] && z.pack[l] <= o_far + z.farf)
+        // in the scratch array the adaptive tree's operands lie over the near
+        // and far partials where they fit: M2L ends before either is written
+        if (scratch && t->ad && z.pack[l] && z.pack[l] <= o_far + z.farf)
             oP[l] = o_near;
         else if (z.pack[l])
             oP[l] = take(z.pack[l]);
     }
-    if (off > (size_t)FMM_NOALLOC_SCRATCH_BYTES)
-        return fail(FMM_EINVAL, "this tree's evaluation needs " + std::to_string(off) +
-                                    " bytes of scratch, more than FMM_NOALLOC_SCRATCH_BYTES (" +
-                                    std::to_string((size_t)FMM_NOALLOC_SCRATCH_BYTES) + ")");
     unsigned char *base = nullptr;
-    HIPCHK(noalloc_scratch((void **)&base));
+    if (scratch) {
+        if (off > (size_t)FMM_NOALLOC_SCRATCH_BYTES)
+            return fail(FMM_EINVAL, "this tree's evaluation needs " + std::to_string(off) +
+                                        " bytes of scratch, more than FMM_NOALLOC_SCRATCH_BYTES (" +
+                                        std::to_string((size_t)FMM_NOALLOC_SCRATCH_BYTES) + ")");
+        HIPCHK(noalloc_scratch((void **)&base));
+    } else {
+        CHK(ensure(t, t->work, off, st));
+        base = (unsigned char *)t->work.p;
+    }
     w.nearf = (double4 *)(base + o_near);
     if (!z.farf) return FMM_OK;
     w.farf = (double4 *)(base + o_far);
@@ -838,7 +884,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     const int Lf = c.max_level;
     if (!t->ad && !(t->ad = new (std::nothrow) AdTree())) return fail(FMM_ENOMEM, "host allocation failed");
     AdTree *a = t->ad;
-    if (!a->hbuf) HIPCHK(hipHostMalloc((void **)&a->hbuf, kAdHostWords * sizeof(uint32_t)));
+    a->hbuf = t->kit.words + 4;
     // the finest keys are sorted themselves (no bin per key of level Lf, so
     // that the cost does not grow with 8^Lf); box ranges come from the
     // sorted keys through the first position of each key of level cl, the
@@ -855,26 +901,15 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
         bound += b;
     }
     const size_t u4 = sizeof(uint32_t);
-    CHK(ensure(t, t->key10, u4 * n, st));
-    CHK(ensure(t, t->counters, 4 * u4, st));
-    CHK(ensure(t, t->perm, u4 * n, st));
-    CHK(ensure(t, t->xyz64, sizeof(double4) * n, st));
-    CHK(ensure(t, t->scan, u4 * scan_scratch_words(bound + 1), st));
-    CHK(ensure(t, a->skey, u4 * n, st));
-    CHK(ensure(t, a->cstart, u4 * (nc + 1), st));
-    CHK(ensure(t, a->ks_a, u4 * n, st));
-    CHK(ensure(t, a->ks_b, u4 * n, st));
-    CHK(ensure(t, a->ks_v, u4 * n, st));
-    CHK(ensure(t, a->ks_h, u4 * (2 * hw + 1 + scan_scratch_words(hw)), st));
-    CHK(ensure(t, a->code, u4 * bound, st));
-    CHK(ensure(t, a->ps, u4 * bound, st));
-    CHK(ensure(t, a->pe, u4 * bound, st));
-    CHK(ensure(t, a->parent, u4 * bound, st));
-    CHK(ensure(t, a->child, 8 * u4 * bound, st));
-    CHK(ensure(t, a->leaf, bound + 4, st));  // read back as whole words by the export
-    CHK(ensure(t, a->cmask, bound, st));
-    CHK(ensure(t, a->nchild, u4 * bound, st));
-    CHK(ensure(t, a->coff, u4 * (bound + 1), st));
+    CHK(place(t, a->area[0],
+              {{&t->key10, u4 * n}, {&t->counters, 4 * u4}, {&t->perm, u4 * n}, {&t->xyz64, sizeof(double4) * n},
+               {&t->scan, u4 * scan_scratch_words(bound + 1)}, {&a->skey, u4 * n}, {&a->cstart, u4 * (nc + 1)},
+               {&a->ks_a, u4 * n}, {&a->ks_b, u4 * n}, {&a->ks_v, u4 * n},
+               {&a->ks_h, u4 * (2 * hw + 1 + scan_scratch_words(hw))}, {&a->code, u4 * bound}, {&a->ps, u4 * bound},
+               {&a->pe, u4 * bound}, {&a->parent, u4 * bound}, {&a->child, 8 * u4 * bound},
+               {&a->leaf, (size_t)bound + 4},  // read back as whole words by the export
+               {&a->cmask, (size_t)bound}, {&a->nchild, u4 * bound}, {&a->coff, u4 * (bound + 1)}},
+              st));
     unsigned int *dc = bp<unsigned int>(t->counters);
     uint32_t *code = bp<uint32_t>(a->code), *ps = bp<uint32_t>(a->ps), *pe = bp<uint32_t>(a->pe);
     int *parent = bp<int>(a->parent), *child = bp<int>(a->child);
@@ -889,8 +924,8 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     ksw.scan = ksw.off + hw + 1;
     const KeyIndex ki{bp<uint32_t>(a->cstart), bp<uint32_t>(a->skey), Lf, cl};
     auto host_read = [&]() -> fmm_status {
-        HIPCHK(hipEventRecord(t->ev_counters, st));
-        HIPCHK(hipEventSynchronize(t->ev_counters));
+        HIPCHK(hipEventRecord(t->kit.ev, st));
+        HIPCHK(hipEventSynchronize(t->kit.ev));
         return FMM_OK;
     };
     HIPCHK(launch_keys(n, dtype, pos, c.box_lo, c.box_size, Lf, bp<uint32_t>(t->key10), nullptr, nullptr, dc, st));
@@ -925,23 +960,19 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     a->nbox = nbox;
     a->nvbox = nlev > 2 ? nbox - a->off[2] : 0;
     if (!t->ops) CHK(build_ops(c.p, &t->ops));
-    CHK(ensure(t, a->lev, u4 * nbox, st));
-    CHK(ensure(t, a->col, 27 * u4 * nbox, st));
-    CHK(ensure(t, a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1), st));
-    CHK(ensure(t, a->offd, sizeof(int64_t) * (nlev + 1), st));
     const int64_t n27 = 27 * nbox;  // (box, direction) pairs of the list passes
-    CHK(ensure(t, a->cnts, 3 * u4 * n27, st));
-    CHK(ensure(t, a->s27, 3 * u4 * (n27 + 1), st));
-    CHK(ensure(t, a->offs, 3 * u4 * (nbox + 1), st));
-    CHK(ensure(t, t->scan, u4 * scan_scratch_words(std::max(3 * n27, n) + 1), st));
-    scan = bp<uint32_t>(t->scan);
-    CHK(ensure(t, a->is_head, u4 * n, st));
-    CHK(ensure(t, a->head, u4 * n, st));
-    CHK(ensure(t, a->hoff, u4 * (n + 1), st));
     // (level, class) groups of the mixed form's M2L targets
     const bool f64 = is_f64_form(t);
     const int ngrp = f64 ? 0 : 8 * std::max(nlev - 2, 0);
-    CHK(ensure(t, a->ccnt, u4 * std::max(ngrp, 1), st));
+    CHK(place(t, a->area[1],
+              {{&a->lev, u4 * nbox}, {&a->col, 27 * u4 * nbox},
+               {&a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1)},
+               {&a->offd, sizeof(int64_t) * (nlev + 1)}, {&a->cnts, 3 * u4 * n27}, {&a->s27, 3 * u4 * (n27 + 1)},
+               {&a->offs, 3 * u4 * (nbox + 1)}, {&t->scan, u4 * scan_scratch_words(std::max(3 * n27, n) + 1)},
+               {&a->is_head, u4 * n}, {&a->head, u4 * n}, {&a->hoff, u4 * (n + 1)},
+               {&a->ccnt, u4 * std::max(ngrp, 1)}},
+              st));
+    scan = bp<uint32_t>(t->scan);
     int *lev = bp<int>(a->lev), *col = bp<int>(a->col), *vidx = bp<int>(a->vidx);
     uint32_t *nu = bp<uint32_t>(a->cnts), *nw = nu + n27, *nx = nw + n27;
     // the U, W and X counts (contiguous) in one scan: run k starts at k n27
@@ -970,27 +1001,24 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     CHK(host_read());
     for (int k = 0; k < 3; ++k) a->nlist[k] = a->hbuf[k];
     a->nleaf = a->hbuf[3];
-    CHK(ensure(t, a->iu, u4 * std::max<int64_t>(a->nlist[0], 1), st));
-    CHK(ensure(t, a->iw, u4 * std::max<int64_t>(a->nlist[1], 1), st));
-    CHK(ensure(t, a->ix, u4 * std::max<int64_t>(a->nlist[2], 1), st));
+    // P2P work units: at most one per leaf plus one per 64 particles
+    a->max_units = a->nleaf + n / 64;
+    CHK(place(t, a->area[2],
+              {{&a->iu, u4 * a->nlist[0]}, {&a->iw, u4 * a->nlist[1]}, {&a->ix, u4 * a->nlist[2]},
+               {&a->lbox, u4 * a->nleaf}, {&a->lstart, u4 * (a->nleaf + 1)}, {&a->llev, (size_t)a->nleaf},
+               {&a->ucnt, u4 * 2 * kAdUnitClasses * a->nleaf}, {&a->uoff, u4 * (2 * kAdUnitClasses * a->nleaf + 1)},
+               {&a->units, sizeof(int2) * a->max_units}, {&a->units_m, sizeof(int2) * a->max_units},
+               {&a->tgt, ngrp ? u4 * a->nvbox : 0}, {&a->goffd, sizeof(int64_t) * (ngrp + 1)}},
+              st));
     HIPCHK(ad_launch_lists(nbox, 1, lev, code, parent, col, child, leaf, nu, nw, nx, su, sw, sx, bp<int>(a->iu),
                            bp<int>(a->iw), bp<int>(a->ix), st));
-    CHK(ensure(t, a->lbox, u4 * a->nleaf, st));
-    CHK(ensure(t, a->lstart, u4 * (a->nleaf + 1), st));
-    CHK(ensure(t, a->llev, a->nleaf, st));
     HIPCHK(launch_zero(dc + 3, 1, st));
     HIPCHK(ad_launch_leaflist(n, a->nleaf, bp<uint32_t>(a->is_head), bp<uint32_t>(a->hoff), bp<int>(a->head), ps,
                               bp<int>(a->lbox), bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev), lev, dc + 3, st));
     HIPCHK(ad_launch_records(n, dtype, bp<uint32_t>(a->hoff), bp<int>(a->lbox), lev, code, bp<uint32_t>(t->perm),
                              pos, c.box_lo, c.box_size, bp<double4>(t->xyz64), st));
-    // P2P work units: at most one per leaf plus one per 64 particles
-    a->max_units = a->nleaf + n / 64;
-    // (heaviest units first: one run of nleaf counts per weight class and
-    // order, P2P over U and M2P over W, and one scan)
-    CHK(ensure(t, a->ucnt, u4 * 2 * kAdUnitClasses * a->nleaf, st));
-    CHK(ensure(t, a->uoff, u4 * (2 * kAdUnitClasses * a->nleaf + 1), st));
-    CHK(ensure(t, a->units, sizeof(int2) * a->max_units, st));
-    CHK(ensure(t, a->units_m, sizeof(int2) * a->max_units, st));
+    // work units, heaviest first: one run of nleaf counts per weight class
+    // and order (P2P over U, M2P over W), and one scan
     HIPCHK(ad_launch_units(a->nleaf, 0, bp<uint32_t>(a->lstart), bp<int>(a->lbox), ou, ow, bp<int>(a->iu), ps, pe,
                            bp<uint32_t>(a->ucnt), nullptr, nullptr, nullptr, st));
     HIPCHK(launch_scan(2 * kAdUnitClasses * a->nleaf, bp<uint32_t>(a->ucnt), bp<uint32_t>(a->uoff), scan, st));
@@ -1033,8 +1061,6 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
         a->fold = fold_plan(c.p, (a->nvbox + tt - 1) / tt, t->ncu, most > pack ? most - pack : 0);
     }
     if (ngrp) {
-        CHK(ensure(t, a->tgt, u4 * a->nvbox, st));
-        CHK(ensure(t, a->goffd, sizeof(int64_t) * (ngrp + 1), st));
         HIPCHK(hipMemcpyAsync(a->goffd.p, a->goff, sizeof(int64_t) * (ngrp + 1), hipMemcpyHostToDevice, st));
         HIPCHK(launch_zero(bp<uint32_t>(a->ccnt), ngrp, st));
         HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, nullptr, bp<int64_t>(a->goffd),
@@ -1217,7 +1243,7 @@ fmm_status evaluate_chain(fmm_tree *t, const void *q, void *phi, void *vec, int3
     const int kind = flags & 3, part = flags & ~3;
     const bool do_far = part != FMM_PART_NEAR_ONLY, do_near = part != FMM_PART_FAR_ONLY;
     Work w;
-    CHK(noalloc ? work_from_scratch(t, do_far, w) : work_from_tree(t, do_far, st, w));
+    CHK(work_buffers(t, do_far, noalloc, st, w));
     // the adaptive kernels leave their results in units of the root box
     const double inv_w = (t->ad ? 1.0 : (double)((int64_t)1 << t->L)) / t->cfg.box_size;
     const Combine c{(const uint32_t *)t->perm.p, (t->L >= 2 && do_far) ? w.farf : nullptr, inv_w, q, phi,
@@ -1234,7 +1260,7 @@ fmm_status evaluate_chain(fmm_tree *t, const void *q, void *phi, void *vec, int3
 fmm_status backward_chain(fmm_tree *t, const void *q, const void *w, const void *field_fwd,
                           void *grad_q, void *grad_pos, hipStream_t st) {
     Work wk;
-    CHK(work_from_tree(t, true, st, wk));
+    CHK(work_buffers(t, true, false, st, wk));
     CHK(t->ad ? run_adaptive(t, wk, w, true, true, true, st) : run_chain(t, wk, w, true, true, true, st));
     const double inv_w = (t->ad ? 1.0 : (double)((int64_t)1 << t->L)) / t->cfg.box_size;
     HIPCHK(launch_combine_grad(t->n, t->dtype, (const uint32_t *)t->perm.p, wk.nearf,
@@ -1340,6 +1366,7 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
     t->cfg = *cfg;
     t->dtype = dtype;
     t->n = n;
+    if (!fresh && st != t->stream) t->strayed = true;
     t->stream = st;
     t->al.fa = cfg->alloc;
     t->al.ff = cfg->free;
@@ -1349,13 +1376,9 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
         t->ncu < 1)
         return bail(fail(FMM_EDEVICE, "cannot read the compute unit count"));
     if (!t->al.fa) ensure_pool(t->dev);
-    if (!t->host_counters) {
-        if (hipHostMalloc((void **)&t->host_counters, 4 * sizeof(unsigned int), hipHostMallocCoherent) !=
-            hipSuccess)
-            return bail(fail(FMM_EDEVICE, "hipHostMalloc failed"));
-        if (hipHostGetDevicePointer((void **)&t->host_counters_dev, t->host_counters, 0) != hipSuccess)
-            return bail(fail(FMM_EDEVICE, "hipHostGetDevicePointer failed"));
-    }
+    if (!t->kit.words && kit_get(t->dev, t->kit) != hipSuccess)
+        return bail(fail(FMM_EDEVICE, "cannot allocate pinned host memory"));
+    t->kit_idle = false;
     fmm_status s;
     // S1: smallest level whose fullest leaf holds <= leaf_max; the coarsest
     // candidate is the first level with 8^l * leaf_max >= n (fewer boxes
@@ -1366,30 +1389,25 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
     // case that the candidate's fullest leaf is over the cap.
     int lev = 0;
     while (lev < cfg->max_level && ((int64_t)1 << (3 * lev)) * (int64_t)cfg->leaf_max < n) ++lev;
-    if (!t->ev_counters && hipEventCreateWithFlags(&t->ev_counters, hipEventDisableTiming) != hipSuccess)
-        return bail(fail(FMM_EDEVICE, "hipEventCreate failed"));
     if (cfg->adaptive) {
         if ((s = build_adaptive(t, n, dtype, pos, st)) != FMM_OK) return bail(s);
+        t->kit_idle = true;
         *out = t;
         return FMM_OK;
     }
     const bool f64 = is_f64_form(t);
-    if ((s = ensure(t, t->key10, sizeof(uint32_t) * n, st)) != FMM_OK) return bail(s);
-    if ((s = ensure(t, t->rank, sizeof(uint32_t) * n, st)) != FMM_OK) return bail(s);
-    if ((s = ensure(t, t->counters, 4 * sizeof(unsigned int), st)) != FMM_OK) return bail(s);
-    if ((s = ensure(t, t->tmp, sizeof(uint32_t) * n, st)) != FMM_OK) return bail(s);
-    if ((s = ensure(t, t->perm, sizeof(uint32_t) * n, st)) != FMM_OK) return bail(s);
-    if (f64) {
-        if ((s = ensure(t, t->xyz64, sizeof(double4) * n, st)) != FMM_OK) return bail(s);
-    } else {
-        if ((s = ensure(t, t->xyz32, sizeof(int4) * n, st)) != FMM_OK) return bail(s);
-    }
+    const size_t nw = sizeof(uint32_t) * (size_t)n;
+    if ((s = place(t, t->parts,
+                   {{&t->key10, nw}, {&t->rank, nw}, {&t->counters, 4 * sizeof(unsigned int)}, {&t->tmp, nw},
+                    {&t->perm, nw}, {f64 ? &t->xyz64 : &t->xyz32, (f64 ? sizeof(double4) : sizeof(int4)) * (size_t)n}},
+                   st)) != FMM_OK)
+        return bail(s);
     auto level_buffers = [&](int l) -> fmm_status {
         const size_t nb = (size_t)1 << (3 * l);
-        fmm_status r;
-        if ((r = ensure(t, t->cnt, sizeof(uint32_t) * nb, st)) != FMM_OK) return r;
-        if ((r = ensure(t, t->start, sizeof(uint32_t) * (nb + 1), st)) != FMM_OK) return r;
-        return ensure(t, t->scan, sizeof(uint32_t) * scan_scratch_words((int64_t)nb), st);
+        return place(t, t->levels,
+                     {{&t->cnt, sizeof(uint32_t) * nb}, {&t->start, sizeof(uint32_t) * (nb + 1)},
+                      {&t->scan, sizeof(uint32_t) * scan_scratch_words((int64_t)nb)}},
+                     st);
     };
     unsigned int *dc = (unsigned int *)t->counters.p;
     // leaf starts (scan of the counts) and the fullest leaf, and the two
@@ -1399,10 +1417,10 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
         bool direct = false;
         hipError_t r = launch_scan_max((int64_t)1 << (3 * l), (const uint32_t *)t->cnt.p,
                                        (uint32_t *)t->start.p, (uint32_t *)t->scan.p, dc + 1, dc,
-                                       t->host_counters_dev, &direct, st);
+                                       t->kit.words_dev, &direct, st);
         if (r == hipSuccess && !direct)
-            r = hipMemcpyAsync(t->host_counters, dc, 2 * sizeof(unsigned int), hipMemcpyDeviceToHost, st);
-        if (r == hipSuccess) r = hipEventRecord(t->ev_counters, st);
+            r = hipMemcpyAsync(t->kit.words, dc, 2 * sizeof(unsigned int), hipMemcpyDeviceToHost, st);
+        if (r == hipSuccess) r = hipEventRecord(t->kit.ev, st);
         return r;
     };
     // placement and the in-leaf ordering (after read_counters at level l)
@@ -1418,12 +1436,12 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
                                (uint32_t *)t->cnt.p, (uint32_t *)t->rank.p, dc, st);
     if (e == hipSuccess) e = read_counters(lev);
     if (e == hipSuccess) e = sort_at(lev);
-    if (e == hipSuccess) e = hipEventSynchronize(t->ev_counters);
+    if (e == hipSuccess) e = hipEventSynchronize(t->kit.ev);
     if (e != hipSuccess) return bail(fail(FMM_EDEVICE, std::string("tree build: ") + hipGetErrorString(e)));
-    if (t->host_counters[0] != 0)
-        return bail(fail(FMM_EDOMAIN, std::to_string(t->host_counters[0]) +
+    if (t->kit.words[0] != 0)
+        return bail(fail(FMM_EDOMAIN, std::to_string(t->kit.words[0]) +
                                           " positions outside the root cube or not finite"));
-    t->max_count = t->host_counters[1];
+    t->max_count = t->kit.words[1];
     if (t->max_count > cfg->leaf_max && lev < cfg->max_level) {
         do {
             ++lev;
@@ -1431,13 +1449,14 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
             e = launch_hist(n, (const uint32_t *)t->key10.p, lev, (uint32_t *)t->cnt.p,
                             (uint32_t *)t->rank.p, dc, st);
             if (e == hipSuccess) e = read_counters(lev);
-            if (e == hipSuccess) e = hipEventSynchronize(t->ev_counters);
+            if (e == hipSuccess) e = hipEventSynchronize(t->kit.ev);
             if (e != hipSuccess) return bail(fail(FMM_EDEVICE, std::string("level selection: ") + hipGetErrorString(e)));
-            t->max_count = t->host_counters[1];
+            t->max_count = t->kit.words[1];
         } while (t->max_count > cfg->leaf_max && lev < cfg->max_level);
         e = sort_at(lev);
         if (e != hipSuccess) return bail(fail(FMM_EDEVICE, std::string("sort: ") + hipGetErrorString(e)));
     }
+    t->kit_idle = true;
     t->L = lev;
     t->nleaf = (int64_t)1 << (3 * lev);
     // translation tables of this p (made once per device and p): a tree with
@@ -1458,6 +1477,7 @@ fmm_status fmm_evaluate(fmm_tree *t, const void *q, void *phi, void *vec, int32_
         return fail(FMM_EINVAL, "unknown flags");
     if (kind != FMM_VEC_NONE && !vec) return fail(FMM_EINVAL, "vec is NULL");
     hipStream_t st = (hipStream_t)stream;
+    if (st != t->stream) t->strayed = true;
     if (!t->cfg.graph) return evaluate_chain(t, q, phi, vec, flags, st);
     const void *arg[5] = {q, phi, vec, nullptr, nullptr};
     if (slot_matches(t, t->gfwd, arg, flags)) return launch_graph(t->gfwd, st);
@@ -1477,6 +1497,7 @@ fmm_status fmm_evaluate_noalloc(fmm_tree *t, const void *q, void *phi, void *vec
     if (t->L >= 2 && !t->ops) return fail(FMM_EINVAL, "the tree has no translation tables");
     // serial order, no events, no graph: nothing here creates a stream, an
     // event or a buffer
+    if ((hipStream_t)stream != t->stream) t->strayed = true;
     t->quiet = true;
     const fmm_status s = evaluate_chain(t, q, phi, vec, flags, (hipStream_t)stream, true);
     t->quiet = false;
@@ -1489,6 +1510,7 @@ fmm_status fmm_backward(fmm_tree *t, const void *q, const void *w, const void *f
     if (grad_pos && !field_fwd) return fail(FMM_EINVAL, "field_fwd is required for grad_pos");
     if (!grad_q && !grad_pos) return FMM_OK;
     hipStream_t st = (hipStream_t)stream;
+    if (st != t->stream) t->strayed = true;
     if (!t->cfg.graph) return backward_chain(t, q, w, field_fwd, grad_q, grad_pos, st);
     const void *arg[5] = {q, w, field_fwd, grad_q, grad_pos};
     if (slot_matches(t, t->gbwd, arg, 0)) return launch_graph(t->gbwd, st);
@@ -1533,12 +1555,9 @@ fmm_status fmm_tree_info(const fmm_tree *tc, fmm_tree_info_t *info) {
         CHK(uniform_counts(t, info));
     }
     size_t ws = 0;
-    const Buf *bufs[] = {&t->key10, &t->rank, &t->cnt, &t->start, &t->tmp, &t->perm, &t->scan,
-                         &t->counters, &t->xyz32, &t->xyz64, &t->nearf, &t->farf, &t->pairs, &t->m2lpart, &t->lmax};
-    for (const Buf *b : bufs) ws += b->cap;
-    for (int l = 0; l <= FMM_MAX_LEVEL; ++l) ws += t->M[l].cap + t->Lc[l].cap + t->pack[l].cap;
+    for (const Buf *b : {&t->parts, &t->levels, &t->work, &t->pairs}) ws += b->cap;
     if (t->ad)
-        for (const Buf *b : t->ad->bufs()) ws += b->cap;
+        for (const Buf &b : t->ad->area) ws += b.cap;
     info->workspace_bytes = ws;
     return FMM_OK;
 }
@@ -1685,17 +1704,12 @@ void fmm_tree_destroy(fmm_tree *t) {
     (void)drop_graph(t->gbwd);
     if (t->cap) (void)hipStreamDestroy(t->cap);
     hipStream_t st = t->stream;
-    Buf *bufs[] = {&t->key10, &t->rank, &t->cnt, &t->start, &t->tmp, &t->perm, &t->scan,
-                   &t->counters, &t->xyz32, &t->xyz64, &t->nearf, &t->farf, &t->pairs, &t->m2lpart, &t->lmax};
-    for (Buf *b : bufs) release(t, *b, st);
-    for (int l = 0; l <= FMM_MAX_LEVEL; ++l) {
-        release(t, t->M[l], st);
-        release(t, t->Lc[l], st);
-        release(t, t->pack[l], st);
-    }
+    // the memory goes back in order on the build's stream: work that another
+    // stream was given on the tree ends first
+    if (t->strayed) (void)hipDeviceSynchronize();
+    for (Buf *b : {&t->parts, &t->levels, &t->work, &t->pairs}) release(t, *b, st);
     if (t->ad) {
-        for (Buf *b : t->ad->bufs()) release(t, *b, st);
-        if (t->ad->hbuf) (void)hipHostFree(t->ad->hbuf);
+        for (Buf &b : t->ad->area) release(t, b, st);
         delete t->ad;
     }
     if (t->ev_ready)
@@ -1707,8 +1721,7 @@ void fmm_tree_destroy(fmm_tree *t) {
         (void)hipEventDestroy(t->ev_fork);
         (void)hipEventDestroy(t->ev_join);
     }
-    if (t->ev_counters) (void)hipEventDestroy(t->ev_counters);
-    if (t->host_counters) (void)hipHostFree(t->host_counters);
+    kit_put(t->kit, t->kit_idle);
     delete t;
 }
 
