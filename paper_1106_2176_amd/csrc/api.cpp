@@ -538,8 +538,8 @@ WorkSizes work_sizes(const fmm_tree *t, bool far) {
         const size_t g = ((size_t)1 << l) + 6;
         z.pack[l] = g * g * g * S * (f64 ? 8 : 4);
     }
-    z.m2lpart = m2l_partial_bytes(P, L, t->ncu);
-    if (f64) z.m2lpart = m2l_fold_partial_bytes(P, L, t->ncu, z.m2lpart);
+    z.m2lpart = f64 ? m2l_fold_partial_bytes(P, L, t->ncu, m2l_partial_cap(P, L, t->ncu))
+                    : m2l_partial_bytes(P, L, t->ncu);
     if (m2l_half(t->cfg)) z.lmax = sizeof(uint32_t) * kLevelSlots;
     return z;
 }
@@ -825,7 +825,7 @@ fmm_status run_chain(fmm_tree *t, const Work &w, const void *charges, bool adjoi
                                       adjoint ? o->atz64 : o->tz64, o->cls, st));
             } else if (f64) {  // dense products, the offsets folded by reflections
                 HIPCHK(launch_m2l_fold(P, L, Bp, Lp, adjoint ? o->afold64 : o->fold64, o->fold, w.m2lpart,
-                                       w.m2lpart_bytes, t->ncu, m2l_partial_bytes(P, L, t->ncu), st));
+                                       w.m2lpart_bytes, t->ncu, m2l_partial_cap(P, L, t->ncu), st));
             } else {  // dense products grouped by offset on the matrix cores
                 const void *A = half ? (const void *)(adjoint ? o->am2lh : o->m2lh)
                                      : (const void *)(adjoint ? o->am2lbf : o->m2lbf);

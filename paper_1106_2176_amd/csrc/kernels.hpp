@@ -290,6 +290,8 @@ hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const 
 // small levels are cut into K parts: `partial` >= m2l_partial_bytes() of FP64
 // scratch.
 size_t m2l_partial_bytes(int P, int L, int ncu);
+// what a tree's partial sums may take in either form
+size_t m2l_partial_cap(int P, int L, int ncu);
 constexpr int kMixedSplit3PMax = 13;  // LDS holds the 3-part operator ring up to p = 13
 // The 2-part bf16 split (about 16 bits per operand) keeps the mixed force
 // within 1e-6 of the FP64 form up to p = 10 only (measured 1.2e-6 at

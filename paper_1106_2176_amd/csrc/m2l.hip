@@ -69,16 +69,21 @@ struct M2LPlan {
     int64_t unit0[kMaxLev + 1];  // first block of each level
     int64_t ntile[kMaxLev];      // tiles of the level (8 classes)
     int nsplit[kMaxLev];         // K parts per tile
-    int64_t part0[kMaxLev];      // first partial slot of the level
+    int64_t part0[kMaxLev];      // first partial column of the level
     const void *B[kMaxLev];      // padded operand grid of the level
     void *L[kMaxLev];            // local expansions of the level
     int out_f64[kMaxLev];
-    int64_t fix0[kMaxLev + 1];   // first fix-up block of each level
+    int64_t fix0[kMaxLev + 1];   // first fix-up column of each level
+    int64_t cap_cols;            // bound of the partial columns of a tree's plan
     // binary16 encoding: per-level maxima (by level) from which the operand
     // scale follows, and the output scale of each row
     const uint32_t *lmax;
     const float *oscale;
 };
+
+// Columns of a level's tiles that hold targets (level 2 has 8 parents, level
+// 3 has 64): only they have partial sums.
+__host__ __device__ inline int tile_cols(int l) { return l < 4 ? 1 << (3 * (l - 1)) : kTile; }
 
 struct M2LUnit {
     int li;         // index into M2LPlan
@@ -519,12 +524,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
                 }
         }
     } else {
-        const int64_t slot = pick(pl.part0, u.li) + (int64_t)u.part * pick(pl.ntile, u.li) + u.tile;
-        double *dst = partial + slot * kTile * P2;
+        double *dst = partial + (pick(pl.part0, u.li) +
+                                 ((int64_t)u.part * pick(pl.ntile, u.li) + u.tile) * tile_cols(l)) * P2;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
+            for (int r = 0; r < RT && cvalid[b]; ++r)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int row = 16 * r + 4 * q + i;
@@ -533,30 +538,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
     }
 }
 
-// Sum of the K parts of a split tile, in part order.  One thread per output
-// coefficient (tile, target column, row).
+// Sum of the K parts of the split tiles, in part order.  One thread per
+// output coefficient (target column, row).
 __global__ __launch_bounds__(256) void k_m2l_fixup(int P, M2LPlan pl, const double *__restrict__ partial,
                                                    int64_t total) {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= total) return;
     const int P2 = P * P, S = coef_stride(P);
-    const int64_t per_tile = (int64_t)kTile * P2;
-    const int64_t ft = g / per_tile;
-    const int e = (int)(g - ft * per_tile);
-    const int li = find_level(pl.fix0, pl.nlev, ft);
-    const int l = pick(pl.level, li), ns = pick(pl.nsplit, li);
-    const int64_t nt = pick(pl.ntile, li), lt = ft - pick(pl.fix0, li);
+    const int64_t fc = g / P2;  // column
+    const int row = (int)(g - fc * P2);
+    const int li = find_level(pl.fix0, pl.nlev, fc);
+    const int l = pick(pl.level, li), ns = pick(pl.nsplit, li), cols = tile_cols(l);
+    const int64_t nt = pick(pl.ntile, li), lc = fc - pick(pl.fix0, li), lt = lc / cols;
     int k;
     int64_t pbase;
     tile_place(l, lt, k, pbase);
-    const int n = 1 << l, h = n >> 1;
-    const int64_t npar = (int64_t)h * h * h;
-    const int c = e / P2, row = e - c * P2;
-    const int64_t pid = pbase + c;
-    if (pid >= npar) return;
-    const double *src = partial + (pick(pl.part0, li) + lt) * per_tile + e;
+    const int n = 1 << l;
+    const int64_t pid = pbase + (lc - lt * cols);
+    const double *src = partial + (pick(pl.part0, li) + lc) * P2 + row;
     double v = 0.0;
-    for (int j = 0; j < ns; ++j) v += src[(int64_t)j * nt * per_tile];
+    for (int j = 0; j < ns; ++j) v += src[(int64_t)j * nt * cols * P2];
     int64_t tpad, trow;
     target_of(pid, k, n, n + 6, S, tpad, trow);
     if (pick(pl.out_f64, li))
@@ -796,61 +797,76 @@ static int64_t level_tiles(int l) {
     return 8 * ((h * h * h + kTile - 1) / kTile);
 }
 
-// Plan: levels largest first.  Levels with at least one tile per CU run
-// unsplit; the others share one split factor s, chosen by simulating the
+// Least simulated time of the small levels' split factor, up to smax: the
 // in-order dispatch of blocks onto ncu one-block-per-CU slots (a whole tile
 // takes time 1, a part 1/s plus a small fixed overhead).
-static M2LPlan compute_plan(int P, int L, bool allow_split, int ncu) {
+static int best_split(int64_t big, int64_t small, int ncu, int nch, int smax) {
+    int best_s = 1;
+    if (small == 0 || ncu <= 0) return best_s;
+    const double ovh = 8.0 / nch;
+    double best_t = 1e300;
+    for (int s = 1; s <= smax; ++s) {
+        std::priority_queue<double, std::vector<double>, std::greater<double>> slots;
+        for (int c = 0; c < ncu; ++c) slots.push(0.0);
+        auto run = [&](int64_t cnt, double dur) {
+            for (int64_t j = 0; j < cnt; ++j) {
+                const double t0 = slots.top();
+                slots.pop();
+                slots.push(t0 + dur);
+            }
+        };
+        run(big, 1.0 + ovh);
+        run(small * s, 1.0 / s + ovh);
+        double t = 0;
+        while (!slots.empty()) {
+            t = slots.top();
+            slots.pop();
+        }
+        if (t < best_t - 1e-9) {
+            best_t = t;
+            best_s = s;
+        }
+    }
+    return best_s;
+}
+
+// Plan: levels largest first.  Levels with at least one tile per CU run
+// unsplit; the others share one split factor: down to one merged group of 8
+// K-steps a part, where a tree has so few tiles that they would leave most
+// of the chip idle, as long as the partial sums (of the columns with targets)
+// take no more memory than whole tiles cut into at most 8 parts of 32 steps
+// would.
+static M2LPlan compute_plan(int P, int L, int ncu) {
     M2LPlan pl{};
     pl.nlev = L - 1;
     const int S = coef_stride(P);
     const int nch = (kOffsetsPerClass * (S / 8) + 3) / 4;  // K-steps of a tile
-    int64_t big = 0, small = 0;
+    int64_t big = 0, small = 0, cols = 0;
     for (int i = 0; i < pl.nlev; ++i) {
         const int l = L - i;
         pl.level[i] = l;
         pl.ntile[i] = level_tiles(l);
-        if (pl.ntile[i] >= ncu) big += pl.ntile[i];
-        else small += pl.ntile[i];
-    }
-    int best_s = 1;
-    if (allow_split && small > 0 && ncu > 0) {
-        const double ovh = 8.0 / nch;
-        double best_t = 1e300;
-        const int smax = std::max(1, std::min(8, nch / 32));
-        for (int s = 1; s <= smax; ++s) {
-            std::priority_queue<double, std::vector<double>, std::greater<double>> slots;
-            for (int c = 0; c < ncu; ++c) slots.push(0.0);
-            auto run = [&](int64_t cnt, double dur) {
-                for (int64_t j = 0; j < cnt; ++j) {
-                    const double t0 = slots.top();
-                    slots.pop();
-                    slots.push(t0 + dur);
-                }
-            };
-            run(big, 1.0 + ovh);
-            run(small * s, 1.0 / s + ovh);
-            double t = 0;
-            while (!slots.empty()) {
-                t = slots.top();
-                slots.pop();
-            }
-            if (t < best_t - 1e-9) {
-                best_t = t;
-                best_s = s;
-            }
+        if (pl.ntile[i] >= ncu) {
+            big += pl.ntile[i];
+        } else {
+            small += pl.ntile[i];
+            cols += pl.ntile[i] * tile_cols(l);
         }
     }
+    const int s8 = best_split(big, small, ncu, nch, std::max(1, std::min(8, nch / 32)));
+    pl.cap_cols = s8 > 1 ? small * s8 * kTile : 0;
+    const int64_t most = cols ? std::max<int64_t>(1, pl.cap_cols / cols) : 1;
+    const int s = best_split(big, small, ncu, nch, (int)std::min<int64_t>(most, (nch + 7) / 8));
     int64_t nu = 0, np = 0, nf = 0;
     for (int i = 0; i < pl.nlev; ++i) {
-        pl.nsplit[i] = pl.ntile[i] >= ncu ? 1 : best_s;
+        pl.nsplit[i] = pl.ntile[i] >= ncu ? 1 : s;
         pl.unit0[i] = nu;
         nu += pl.ntile[i] * pl.nsplit[i];
         pl.part0[i] = np;
         pl.fix0[i] = nf;
         if (pl.nsplit[i] > 1) {
-            np += pl.ntile[i] * pl.nsplit[i];
-            nf += pl.ntile[i];
+            np += pl.ntile[i] * pl.nsplit[i] * tile_cols(pl.level[i]);
+            nf += pl.ntile[i] * tile_cols(pl.level[i]);
         }
     }
     pl.unit0[pl.nlev] = nu;
@@ -858,25 +874,29 @@ static M2LPlan compute_plan(int P, int L, bool allow_split, int ncu) {
     return pl;
 }
 
-// The plan depends only on (p, L, split allowed, CU count); the dispatch
-// simulation costs tens of microseconds of host time, so plans are memoised.
-static M2LPlan make_plan(int P, int L, bool allow_split, int ncu) {
+// The plan depends only on (p, L, CU count); the dispatch simulation costs
+// tens of microseconds of host time, so plans are memoised.
+static M2LPlan make_plan(int P, int L, int ncu) {
     static std::mutex mu;
-    static std::map<std::tuple<int, int, bool, int>, M2LPlan> memo;
-    const auto key = std::make_tuple(P, L, allow_split, ncu);
+    static std::map<std::tuple<int, int, int>, M2LPlan> memo;
+    const auto key = std::make_tuple(P, L, ncu);
     std::lock_guard<std::mutex> g(mu);
     auto it = memo.find(key);
-    if (it == memo.end()) it = memo.emplace(key, compute_plan(P, L, allow_split, ncu)).first;
+    if (it == memo.end()) it = memo.emplace(key, compute_plan(P, L, ncu)).first;
     return it->second;
 }
 
 size_t m2l_partial_bytes(int P, int L, int ncu) {
     if (L < 2) return 0;
-    const M2LPlan pl = make_plan(P, L, true, ncu);
+    const M2LPlan pl = make_plan(P, L, ncu);
     int64_t np = 0;
     for (int i = 0; i < pl.nlev; ++i)
-        if (pl.nsplit[i] > 1) np += pl.ntile[i] * pl.nsplit[i];
-    return (size_t)np * kTile * P * P * sizeof(double);
+        if (pl.nsplit[i] > 1) np += pl.ntile[i] * pl.nsplit[i] * tile_cols(pl.level[i]);
+    return (size_t)np * P * P * sizeof(double);
+}
+
+size_t m2l_partial_cap(int P, int L, int ncu) {
+    return L < 2 ? 0 : (size_t)make_plan(P, L, ncu).cap_cols * P * P * sizeof(double);
 }
 
 // Eight waves (two per SIMD) wherever their operator ring fits in LDS; four
@@ -895,7 +915,7 @@ static void launch_bf16(unsigned nb, const M2LPlan &pl, const uint16_t *A, size_
 static hipError_t fixup(int P, const M2LPlan &pl, unsigned nfix, const double *partial, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nfix == 0) return e;
-    const int64_t total = (int64_t)nfix * kTile * P * P;
+    const int64_t total = (int64_t)nfix * P * P;
     k_m2l_fixup<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(P, pl, partial, total);
     return hipGetLastError();
 }
@@ -904,7 +924,7 @@ hipError_t launch_m2l(int P, int L, int nsplit, void *const *B, void *const *Lc,
                       double *partial, size_t partial_bytes, int ncu, const M2LHalf *half,
                       hipStream_t st) {
     if (L < 2) return hipSuccess;
-    M2LPlan pl = make_plan(P, L, true, ncu);
+    M2LPlan pl = make_plan(P, L, ncu);
     pl.lmax = half ? half->lmax : nullptr;
     pl.oscale = half ? half->oscale : nullptr;
     for (int i = 0; i < pl.nlev; ++i) {
