@@ -3,10 +3,10 @@
 //
 // Tree.  Particles are counting-sorted by their Morton key at the finest
 // level Lf (stable, ties in input order), so every box of every level is one
-// contiguous range of the sorted order.  Level by level, a box holding more
-// than leaf_max particles (below Lf) is split and its non-empty children are
-// appended to the next level in Morton order; the rest are leaves.  Box ids
-// are global (levels concatenated, breadth first), box 0 is the root.
+// contiguous range of the sorted order.  A box holding more than leaf_max
+// particles (below Lf) is split into its non-empty children; the rest are
+// leaves.  Box ids are global (levels concatenated, each in Morton order),
+// box 0 is the root.
 //
 // Lists, for box b (colleagues: the boxes of b's own level at offsets -1..1;
 // two boxes are adjacent when their closed cubes touch and neither contains
@@ -96,13 +96,6 @@ __device__ __forceinline__ bool ad_touch(const AdBox a, const AdBox b) {
     return !inside;
 }
 
-__global__ void k_ad_root(uint32_t n, uint32_t *code, uint32_t *ps, uint32_t *pe, int *parent) {
-    code[0] = 0;
-    ps[0] = 0;
-    pe[0] = n;
-    parent[0] = -1;
-}
-
 // The first sorted position whose key at the finest level Lf is >= x (x in
 // [0, 8^Lf]): the table entry when x is a key of level cl, else a binary
 // search of the sorted keys between the entries of x's level-cl key.
@@ -122,112 +115,214 @@ __device__ __forceinline__ uint32_t key_start(const KeyIndex &ki, uint64_t x) {
     return lo;
 }
 
-// Split decision and the non-empty children of the level's boxes [b0, b0+nb).
-__global__ void k_ad_count(int64_t b0, int64_t nb, int l, int Lf, int leaf_max, const uint32_t *__restrict__ code,
-                           const uint32_t *__restrict__ ps, const uint32_t *__restrict__ pe, const KeyIndex ki,
-                           uint8_t *__restrict__ leaf, uint32_t *__restrict__ nchild, uint8_t *__restrict__ cmask) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nb) return;
-    const int64_t g = b0 + i;
-    const bool split = pe[g] - ps[g] > (uint32_t)leaf_max && l < Lf;
-    uint32_t k = 0, mask = 0;
-    if (split) {
-        const int sh = 3 * (Lf - l - 1);
-        const uint64_t m0 = (uint64_t)code[g] << 3;
-        uint32_t s = key_start(ki, m0 << sh);
-        for (uint32_t c = 0; c < 8; ++c) {
-            const uint32_t e = key_start(ki, (m0 + c + 1) << sh);
-            if (e > s) {
-                mask |= 1u << c;
-                ++k;
+// The boxes in one pass over the sorted particles.  Let S(i) be the finest
+// level below Lf at which the box of particle i holds more than leaf_max
+// particles (-1: none); the counts fall with the level, so every coarser box
+// around i is split as well, i's leaf is at level S(i) + 1, and the boxes
+// around i are those of the levels 0..S(i) + 1.  With c the number of levels
+// at which i shares its box with particle i - 1 (0 for the first particle),
+// i is the first particle of exactly its boxes of the levels c..S(i) + 1.
+// So the boxes of a level, in Morton order, are the particles that head one,
+// and a scan of their counts per (level, block of particles), level-major,
+// numbers the boxes breadth first; one more row counts the leaves.
+//
+// Both kernels are bound by the latency of their loads (n = 1e6, 32 particles
+// per leaf on average, levels to 10: 36 and 16 us).  They stand for a count,
+// a scan, a fill and a host read of the child count per level, eleven times:
+// the whole build took 1.23 ms with those and takes 0.64 ms.
+constexpr int kAdBoxWaves = 4;  // waves per block, each on 256 consecutive particles
+static_assert(kAdBoxBlock == 256 * kAdBoxWaves, "four chunks of 64 particles per wave");
+
+// span[i] = c | (leaf level) << 4, and the block's counts per row
+__global__ __launch_bounds__(64 * kAdBoxWaves) void k_ad_spans(int64_t n, int64_t nblk, int Lf, uint32_t leaf_max,
+                                                               const KeyIndex ki, uint8_t *__restrict__ span,
+                                                               uint32_t *__restrict__ cnt) {
+    __shared__ uint32_t sum[kAdBoxWaves][FMM_MAX_LEVEL + 2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * kAdBoxBlock + 256 * wave + lane;
+    int first[4], last[4], hi[4];  // levels headed; none beyond n
+    uint32_t key[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int64_t i = std::min(i0 + 64 * c, n - 1);
+        key[c] = ki.skey[i];
+        const uint32_t x = i > 0 ? key[c] ^ ki.skey[i - 1] : 0u;
+        first[c] = i == 0 ? 0 : x ? Lf - (31 - __clz((int)x)) / 3 : Lf + 1;
+        last[c] = -1;  // S lies in [last, hi)
+        hi[c] = Lf;
+    }
+    // the four searches side by side: a step halves every hi - last above 1
+    for (int w = Lf + 1; w > 1; w = (w + 1) / 2) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (hi[c] - last[c] <= 1) continue;
+            const int l = (last[c] + hi[c]) >> 1, sh = 3 * (Lf - l);
+            const uint64_t b = key[c] >> sh;
+            const bool over = key_start(ki, (b + 1) << sh) - key_start(ki, b << sh) > leaf_max;
+            last[c] = over ? l : last[c];
+            hi[c] = over ? hi[c] : l;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int64_t i = i0 + 64 * c;
+        ++last[c];
+        if (i < n) span[i] = (uint8_t)(first[c] | last[c] << 4);
+        if (i >= n) first[c] = last[c] + 1;
+    }
+    for (int r = 0; r <= Lf + 1; ++r) {
+        uint32_t k = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            k += (uint32_t)__popcll(__ballot(r <= Lf ? first[c] <= r && r <= last[c] : first[c] <= last[c]));
+        if (lane == 0) sum[wave][r] = k;
+    }
+    __syncthreads();
+    for (int r = threadIdx.x; r <= Lf + 1; r += 64 * kAdBoxWaves) {
+        uint32_t k = 0;
+        for (int w = 0; w < kAdBoxWaves; ++w) k += sum[w][r];
+        cnt[r * nblk + blockIdx.x] = k;
+    }
+}
+
+// The scanned counts' row starts (the first box of every level, then nbox and
+// the total of boxes and leaves) and the count of bad positions, for the host.
+__global__ void k_ad_sizes(int64_t nblk, int Lf, const uint32_t *__restrict__ base, const unsigned int *nbad,
+                           unsigned int *__restrict__ host) {
+    const int r = threadIdx.x;
+    if (r <= Lf + 2) host[r] = base[r * nblk];
+    if (r == Lf + 3) host[r] = *nbad;
+}
+
+// The boxes and the leaf list from the spans and the scanned counts.
+// child[8 g] is left at the first child of a split box g, -1 for a leaf.
+__global__ __launch_bounds__(64 * kAdBoxWaves) void k_ad_boxes(int64_t n, int64_t nblk, int Lf, int64_t nbox,
+                                                               int64_t nleaf, const KeyIndex ki,
+                                                               const uint8_t *__restrict__ span,
+                                                               const uint32_t *__restrict__ base, AdBoxes bx) {
+    __shared__ uint32_t sum[kAdBoxWaves][FMM_MAX_LEVEL + 2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i0 = (int64_t)blockIdx.x * kAdBoxBlock + 256 * wave + lane;
+    const uint64_t below = ((uint64_t)1 << lane) - 1;
+    int first[4], last[4];
+    uint32_t key[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int64_t i = i0 + 64 * c;
+        const uint32_t sp = i < n ? span[i] : 1u;
+        key[c] = i < n ? ki.skey[i] : 0u;
+        first[c] = (int)(sp & 15);
+        last[c] = (int)(sp >> 4);
+    }
+    for (int r = 0; r <= Lf + 1; ++r) {
+        uint32_t k = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            k += (uint32_t)__popcll(__ballot(r <= Lf ? first[c] <= r && r <= last[c] : first[c] <= last[c]));
+        if (lane == 0) sum[wave][r] = k;
+    }
+    __syncthreads();
+    auto start = [&](int r) {  // rank of the wave's first particle in row r
+        uint32_t k = base[r * nblk + blockIdx.x];
+        for (int w = 0; w < wave; ++w) k += sum[w][r];
+        return k;
+    };
+    uint32_t leaf[4], above[4];  // the leaf's index; the box of the level above around the particle
+    {
+        uint32_t run = start(Lf + 1) - (uint32_t)nbox;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint64_t m = __ballot(first[c] <= last[c]);
+            leaf[c] = run + (uint32_t)__popcll(m & below);
+            run += (uint32_t)__popcll(m);
+        }
+    }
+    for (int r = 0; r <= Lf; ++r) {
+        uint32_t run = start(r);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int64_t i = i0 + 64 * c;
+            const bool head = first[c] <= r && r <= last[c];
+            const uint64_t m = __ballot(head);
+            const uint32_t id = run + (uint32_t)__popcll(m & below);
+            run += (uint32_t)__popcll(m);
+            if (head) {
+                bx.code[id] = key[c] >> (3 * (Lf - r));
+                bx.ps[id] = (uint32_t)i;
+                bx.lev[id] = r;
+                bx.leaf[id] = r == last[c];
+                bx.parent[id] = r > 0 ? (int)above[c] : -1;
+                if (r > first[c]) bx.child[8 * (int64_t)above[c]] = (int)id;
+                if (r == last[c]) {
+                    bx.child[8 * (int64_t)id] = -1;
+                    bx.lbox[leaf[c]] = (int)id;
+                    bx.lstart[leaf[c]] = (uint32_t)i;
+                    bx.llev[leaf[c]] = (uint8_t)r;
+                }
             }
-            s = e;
+            above[c] = head ? id : id - 1;  // not used where no particle before heads a box of level r
         }
     }
-    leaf[g] = split ? 0 : 1;
-    nchild[i] = k;
-    cmask[g] = (uint8_t)mask;
+    if (blockIdx.x == 0 && threadIdx.x == 0) bx.lstart[nleaf] = (uint32_t)n;
 }
 
-// Append the children of level l's boxes at global ids next0 + coff[i] ...
-__global__ void k_ad_children(int64_t b0, int64_t nb, int l, int Lf, int64_t next0, const KeyIndex ki,
-                              const uint32_t *__restrict__ coff,
-                              const uint8_t *__restrict__ cmask, uint32_t *__restrict__ code,
-                              uint32_t *__restrict__ ps, uint32_t *__restrict__ pe, int *__restrict__ parent,
-                              int *__restrict__ child) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nb) return;
-    const int64_t g = b0 + i;
-    const uint32_t mask = cmask[g];
-    int64_t j = next0 + coff[i];
-    const int sh = 3 * (Lf - l - 1);
+// The end of every box's range, and its children: the boxes from the first
+// child on (found by k_ad_boxes) whose parent it is, at most eight.
+__global__ __launch_bounds__(256) void k_ad_links(int64_t nbox, const KeyIndex ki, AdBoxes bx) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= nbox) return;
+    bx.pe[g] = key_start(ki, ((uint64_t)bx.code[g] + 1) << (3 * (ki.Lf - bx.lev[g])));
+    int64_t j = bx.child[8 * g];
+    if (j < 0) j = nbox;
     for (uint32_t c = 0; c < 8; ++c) {
-        if (!((mask >> c) & 1u)) {
-            child[8 * g + c] = -1;
-            continue;
-        }
-        const uint64_t m = ((uint64_t)code[g] << 3) | c;
-        code[j] = (uint32_t)m;
-        ps[j] = key_start(ki, m << sh);
-        pe[j] = key_start(ki, (m + 1) << sh);
-        parent[j] = (int)g;
-        child[8 * g + c] = (int)j;
-        ++j;
+        int r = -1;
+        if (j < nbox && bx.parent[j] == (int)g && (bx.code[j] & 7u) == c) r = (int)j++;
+        bx.child[8 * g + c] = r;
     }
 }
 
-// Colleagues (the 27 same-level boxes at offsets -1..1, -1 if absent) of the
-// level's boxes, by binary search in the level's Morton-sorted codes; one
-// thread per (box, offset).
-__global__ void k_ad_colleagues(int64_t b0, int64_t nb, int l, const uint32_t *__restrict__ code,
-                                int *__restrict__ col) {
+// Colleagues (the 27 same-level boxes at offsets -1..1, -1 if absent) of
+// every box, one thread per (box, offset): down from the root along the
+// target's Morton code, at most a load per level, the top ones shared.
+__global__ __launch_bounds__(256) void k_ad_colleagues(int64_t nbox, const int *__restrict__ lev,
+                                                       const uint32_t *__restrict__ code,
+                                                       const int *__restrict__ child, int *__restrict__ col) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 27 * nb) return;
-    const int64_t g = b0 + i / 27;
-    const int o = (int)(i % 27);
-    int64_t x, y, z;
-    box_coords(code[g], x, y, z);
-    const int64_t side = (int64_t)1 << l;
-    const int64_t sx = x + o % 3 - 1, sy = y + (o / 3) % 3 - 1, sz = z + o / 9 - 1;
+    if (i >= 27 * nbox) return;
+    const int64_t g = i / 27;
+    const int o = (int)(i - 27 * g), l = lev[g];
+    const AdBox b = ad_box(l, code[g]);
+    const int side = 1 << l;
+    const int sx = b.x + o % 3 - 1, sy = b.y + (o / 3) % 3 - 1, sz = b.z + o / 9 - 1;
     int r = -1;
     if (sx >= 0 && sy >= 0 && sz >= 0 && sx < side && sy < side && sz < side) {
         const uint32_t key = morton3((uint32_t)sx, (uint32_t)sy, (uint32_t)sz);
-        int64_t lo = b0, hi = b0 + nb - 1;
-        while (lo <= hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            const uint32_t k = code[mid];
-            if (k == key) {
-                r = (int)mid;
-                break;
-            }
-            if (k < key) lo = mid + 1;
-            else hi = mid - 1;
-        }
+        r = 0;
+        for (int k = l - 1; k >= 0 && r >= 0; --k) r = child[8 * (int64_t)r + ((key >> (3 * k)) & 7u)];
     }
-    col[27 * g + o] = r;
+    col[i] = r;
 }
 
-// V as slots: for box g of level l >= 2 and class k (its coordinate parities),
-// slot s of the class's 189 offsets holds the source box t + d if it exists
-// (a child of one of the parent's colleagues), else -1; one thread per
-// (box, slot).
-__global__ void k_ad_vslots(int64_t b0, int64_t nb, const uint32_t *__restrict__ code,
-                            const int *__restrict__ parent, const int *__restrict__ col,
-                            const int *__restrict__ child, const int2 *__restrict__ cls,
-                            int *__restrict__ vidx) {
+// V as slots: for box g of level >= 2 (g >= box2) and class k (its coordinate
+// parities), slot s of the class's 189 offsets holds the source box t + d if
+// it exists (a child of one of the parent's colleagues), else -1; one thread
+// per (box, slot).
+__global__ __launch_bounds__(256) void k_ad_vslots(int64_t box2, int64_t nb, const uint32_t *__restrict__ code,
+                                                   const int *__restrict__ parent, const int *__restrict__ col,
+                                                   const int *__restrict__ child, const int2 *__restrict__ cls,
+                                                   int *__restrict__ vidx) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)kOffsetsPerClass * nb) return;
     const int64_t bi = i / kOffsetsPerClass;
     const int s = (int)(i - bi * kOffsetsPerClass);
-    const int64_t g = b0 + bi;
-    int64_t tx, ty, tz;
-    box_coords(code[g], tx, ty, tz);
-    const int k = (int)((tx & 1) | ((ty & 1) << 1) | ((tz & 1) << 2));
+    const int64_t g = box2 + bi;
+    const AdBox t = ad_box(0, code[g]);
+    const int k = (t.x & 1) | ((t.y & 1) << 1) | ((t.z & 1) << 2);
     const int e = cls[k * kOffsetsPerClass + s].x;
-    const int64_t sx = tx + (e & 15) - 4, sy = ty + ((e >> 4) & 15) - 4, sz = tz + ((e >> 8) & 15) - 4;
+    const int sx = t.x + (e & 15) - 4, sy = t.y + ((e >> 4) & 15) - 4, sz = t.z + ((e >> 8) & 15) - 4;
     int r = -1;
     if (sx >= 0 && sy >= 0 && sz >= 0) {
-        const int64_t ox = (sx >> 1) - (tx >> 1), oy = (sy >> 1) - (ty >> 1), oz = (sz >> 1) - (tz >> 1);
+        const int ox = (sx >> 1) - (t.x >> 1), oy = (sy >> 1) - (t.y >> 1), oz = (sz >> 1) - (t.z >> 1);
         const int pc = col[27 * (int64_t)parent[g] + (ox + 1) + 3 * (oy + 1) + 9 * (oz + 1)];
         if (pc >= 0) r = child[8 * (int64_t)pc + ((sx & 1) | ((sy & 1) << 1) | ((sz & 1) << 2))];
     }
@@ -324,50 +419,24 @@ __global__ void k_ad_lists(int64_t nbox, int pass, const int *__restrict__ lev, 
 }
 
 // Per-box list offsets from the per-(box, direction) scans: box g starts at
-// its direction 0 (g = nbox: the totals).
+// its direction 0 (g = nbox: the totals, also for the host, with the ngrp
+// group counts of the M2L targets).
 __global__ void k_ad_box_offsets(int64_t nbox, const uint32_t *__restrict__ s27, uint32_t *__restrict__ ou,
-                                 uint32_t *__restrict__ ow, uint32_t *__restrict__ ox) {
+                                 uint32_t *__restrict__ ow, uint32_t *__restrict__ ox, int ngrp,
+                                 const unsigned int *__restrict__ ccnt, unsigned int *__restrict__ host) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < ngrp) host[3 + g] = ccnt[g];
     if (g > nbox) return;
     const int64_t m = 27 * nbox;  // one scan of the U, W and X counts: run k starts at s27[k m]
-    ou[g] = s27[27 * g];
-    ow[g] = s27[m + 27 * g] - s27[m];
-    ox[g] = s27[2 * m + 27 * g] - s27[2 * m];
-}
-
-// level of every box from the level offsets
-__global__ void k_ad_levels(int64_t nbox, const int64_t *__restrict__ off, int nlev, int *__restrict__ lev) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= nbox) return;
-    int l = 0;
-    for (int j = 1; j < nlev; ++j)
-        if (g >= off[j]) l = j;
-    lev[g] = l;
-}
-
-// Leaves in particle order: head[ps] = leaf id, compacted by a scan
-__global__ void k_ad_heads(int64_t nbox, const uint8_t *__restrict__ leaf, const uint32_t *__restrict__ ps,
-                           const uint32_t *__restrict__ pe, uint32_t *__restrict__ is_head,
-                           int *__restrict__ head) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= nbox || !leaf[g]) return;
-    is_head[ps[g]] = 1u;
-    head[ps[g]] = (int)g;
-}
-__global__ void k_ad_leaflist(int64_t n, const uint32_t *__restrict__ is_head, const uint32_t *__restrict__ hoff,
-                              const int *__restrict__ head, const uint32_t *__restrict__ ps,
-                              int *__restrict__ lbox, uint32_t *__restrict__ lstart, uint8_t *__restrict__ llev,
-                              const int *__restrict__ lev) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (is_head[i]) {
-        const uint32_t j = hoff[i];
-        const int g = head[i];
-        lbox[j] = g;
-        lstart[j] = ps[g];
-        llev[j] = (uint8_t)lev[g];
+    const uint32_t u = s27[27 * g], w = s27[m + 27 * g] - s27[m], x = s27[2 * m + 27 * g] - s27[2 * m];
+    ou[g] = u;
+    ow[g] = w;
+    ox[g] = x;
+    if (g == nbox) {
+        host[0] = u;
+        host[1] = w;
+        host[2] = x;
     }
-    if (i == n - 1) lstart[hoff[n]] = (uint32_t)n;
 }
 
 // The fullest leaf: a block maximum over a grid stride, one atomic per block.
@@ -461,19 +530,16 @@ __global__ void k_ad_counts(int64_t nbox, int64_t box2, const uint8_t *__restric
     if (xs) atomicAdd(out + 3, xs);
 }
 
-// Sorted records relative to each particle's leaf (leaf units, FP64); the
-// leaf of sorted position i is the last leaf head at or before i.
+// Sorted records relative to each particle's leaf (leaf units, FP64).
 template <typename Tin>
-__global__ void k_ad_records(int64_t n, const uint32_t *__restrict__ hoff, const int *__restrict__ lbox,
-                             const int *__restrict__ lev, const uint32_t *__restrict__ code,
+__global__ void k_ad_records(int64_t n, int Lf, const uint8_t *__restrict__ span, const uint32_t *__restrict__ skey,
                              const uint32_t *__restrict__ perm, const Tin *__restrict__ pos, double lo0,
                              double lo1, double lo2, double inv_size, double4 *__restrict__ rec) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int g = lbox[hoff[i + 1] - 1];
-    const int l = lev[g];
+    const int l = span[i] >> 4;
     int64_t bx, by, bz;
-    box_coords(code[g], bx, by, bz);
+    box_coords(skey[i] >> (3 * (Lf - l)), bx, by, bz);
     const double sc = (double)((int64_t)1 << l) * inv_size;
     const uint32_t o = perm[i];
     double4 r;
@@ -1194,7 +1260,7 @@ __global__ void k_ad_m2l_sum(AdM2LPlan pl, int P2, int S, const int *__restrict_
 // change any result).
 __global__ __launch_bounds__(256) void k_ad_class(int64_t box2, int64_t nb, const int *__restrict__ lev,
                                                   const uint32_t *__restrict__ code, unsigned int *__restrict__ cnt,
-                                                  const int64_t *__restrict__ goff, unsigned int *__restrict__ fill,
+                                                  const AdGroupStarts gs, unsigned int *__restrict__ fill,
                                                   int *__restrict__ tgt) {
     __shared__ unsigned int h[kAdMaxGroups], base[kAdMaxGroups];
     for (int k = threadIdx.x; k < kAdMaxGroups; k += 256) h[k] = 0;
@@ -1213,7 +1279,7 @@ __global__ __launch_bounds__(256) void k_ad_class(int64_t box2, int64_t nb, cons
     for (int k = threadIdx.x; k < kAdMaxGroups; k += 256)
         if (h[k]) base[k] = atomicAdd(fill ? fill + k : cnt + k, h[k]);
     __syncthreads();
-    if (fill && grp >= 0) tgt[goff[grp] + base[grp] + rank] = (int)(box2 + i);
+    if (fill && grp >= 0) tgt[gs.at[grp] + base[grp] + rank] = (int)(box2 + i);
 }
 
 // ------------------------------------------------ M2L, binary16 encoding
@@ -1496,41 +1562,31 @@ __global__ __launch_bounds__(256) void k_ad_m2l_h(AdM2LPlan pl, const uint16_t *
 // ---------------------------------------------------------- host helpers
 static inline unsigned ad_blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-hipError_t ad_launch_root(uint32_t n, uint32_t *code, uint32_t *ps, uint32_t *pe, int *parent, hipStream_t st) {
-    k_ad_root<<<1, 1, 0, st>>>(n, code, ps, pe, parent);
+int64_t ad_box_blocks(int64_t n) { return (n + kAdBoxBlock - 1) / kAdBoxBlock; }
+
+hipError_t ad_launch_spans(int64_t n, int leaf_max, const KeyIndex &ki, uint8_t *span, uint32_t *cnt, uint32_t *base,
+                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, hipStream_t st) {
+    const int64_t nblk = ad_box_blocks(n);
+    k_ad_spans<<<(unsigned)nblk, 64 * kAdBoxWaves, 0, st>>>(n, nblk, ki.Lf, (uint32_t)leaf_max, ki, span, cnt);
+    hipError_t e = launch_scan((ki.Lf + 2) * nblk, cnt, base, scan, st);
+    if (e != hipSuccess) return e;
+    k_ad_sizes<<<1, 64, 0, st>>>(nblk, ki.Lf, base, nbad, host);
     return hipGetLastError();
 }
 
-hipError_t ad_launch_count(int64_t b0, int64_t nb, int l, int Lf, int leaf_max, const uint32_t *code,
-                           const uint32_t *ps, const uint32_t *pe, const KeyIndex &ki, uint8_t *leaf,
-                           uint32_t *nchild, uint8_t *cmask, hipStream_t st) {
-    k_ad_count<<<ad_blocks(nb, 256), 256, 0, st>>>(b0, nb, l, Lf, leaf_max, code, ps, pe, ki, leaf, nchild, cmask);
+hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyIndex &ki, const uint8_t *span,
+                           const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st) {
+    const int64_t nblk = ad_box_blocks(n);
+    k_ad_boxes<<<(unsigned)nblk, 64 * kAdBoxWaves, 0, st>>>(n, nblk, ki.Lf, nbox, nleaf, ki, span, base, bx);
+    k_ad_links<<<ad_blocks(nbox, 256), 256, 0, st>>>(nbox, ki, bx);
+    k_ad_colleagues<<<ad_blocks(27 * nbox, 256), 256, 0, st>>>(nbox, bx.lev, bx.code, bx.child, col);
     return hipGetLastError();
 }
 
-hipError_t ad_launch_children(int64_t b0, int64_t nb, int l, int Lf, int64_t next0, const KeyIndex &ki,
-                              const uint32_t *coff, const uint8_t *cmask, uint32_t *code, uint32_t *ps,
-                              uint32_t *pe, int *parent, int *child, hipStream_t st) {
-    k_ad_children<<<ad_blocks(nb, 256), 256, 0, st>>>(b0, nb, l, Lf, next0, ki, coff, cmask, code, ps, pe, parent,
-                                                       child);
-    return hipGetLastError();
-}
-
-hipError_t ad_launch_structure(int64_t nbox, int nlev, const int64_t *off_host, const int64_t *off_dev,
-                               const uint32_t *code, const int *parent, const int *child, int *lev, int *col,
-                               const int2 *cls, int *vidx, hipStream_t st) {
-    k_ad_levels<<<ad_blocks(nbox, 256), 256, 0, st>>>(nbox, off_dev, nlev, lev);
-    for (int l = 0; l < nlev; ++l) {
-        const int64_t nb = off_host[l + 1] - off_host[l];
-        if (nb > 0) k_ad_colleagues<<<ad_blocks(27 * nb, 256), 256, 0, st>>>(off_host[l], nb, l, code, col);
-    }
-    for (int l = 2; l < nlev; ++l) {
-        const int64_t nb = off_host[l + 1] - off_host[l];
-        if (nb > 0)
-            k_ad_vslots<<<ad_blocks(kOffsetsPerClass * nb, 256), 256, 0, st>>>(off_host[l], nb, code, parent, col,
-                                                                                child, cls,
-                                                             vidx + 189 * (off_host[l] - off_host[2]));
-    }
+hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const uint32_t *code, const int *parent, const int *col,
+                            const int *child, const int2 *cls, int *vidx, hipStream_t st) {
+    if (nb == 0) return hipSuccess;
+    k_ad_vslots<<<ad_blocks(kOffsetsPerClass * nb, 256), 256, 0, st>>>(box2, nb, code, parent, col, child, cls, vidx);
     return hipGetLastError();
 }
 
@@ -1544,21 +1600,13 @@ hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_
 }
 
 hipError_t ad_launch_box_offsets(int64_t nbox, const uint32_t *s27, uint32_t *ou, uint32_t *ow, uint32_t *ox,
-                                 hipStream_t st) {
-    k_ad_box_offsets<<<ad_blocks(nbox + 1, 256), 256, 0, st>>>(nbox, s27, ou, ow, ox);
+                                 int ngrp, const unsigned int *ccnt, unsigned int *host, hipStream_t st) {
+    k_ad_box_offsets<<<ad_blocks(std::max<int64_t>(nbox + 1, ngrp), 256), 256, 0, st>>>(nbox, s27, ou, ow, ox, ngrp,
+                                                                                        ccnt, host);
     return hipGetLastError();
 }
 
-hipError_t ad_launch_heads(int64_t nbox, const uint8_t *leaf, const uint32_t *ps, const uint32_t *pe,
-                           uint32_t *is_head, int *head, hipStream_t st) {
-    k_ad_heads<<<ad_blocks(nbox, 256), 256, 0, st>>>(nbox, leaf, ps, pe, is_head, head);
-    return hipGetLastError();
-}
-
-hipError_t ad_launch_leaflist(int64_t n, int64_t nleaf, const uint32_t *is_head, const uint32_t *hoff,
-                              const int *head, const uint32_t *ps, int *lbox, uint32_t *lstart, uint8_t *llev,
-                              const int *lev, unsigned int *mx, hipStream_t st) {
-    k_ad_leaflist<<<ad_blocks(n, 256), 256, 0, st>>>(n, is_head, hoff, head, ps, lbox, lstart, llev, lev);
+hipError_t ad_launch_leafmax(int64_t nleaf, const uint32_t *lstart, unsigned int *mx, hipStream_t st) {
     k_ad_leafmax<<<(unsigned)std::min<int64_t>(256, (nleaf + 255) / 256), 256, 0, st>>>(nleaf, lstart, mx);
     return hipGetLastError();
 }
@@ -1570,15 +1618,15 @@ hipError_t ad_launch_counts(int64_t nbox, int64_t box2, const uint8_t *leaf, con
     return hipGetLastError();
 }
 
-hipError_t ad_launch_records(int64_t n, int dtype, const uint32_t *hoff, const int *lbox, const int *lev,
-                             const uint32_t *code, const uint32_t *perm, const void *pos, const double lo[3],
-                             double size, double4 *rec, hipStream_t st) {
+hipError_t ad_launch_records(int64_t n, int dtype, int Lf, const uint8_t *span, const uint32_t *skey,
+                             const uint32_t *perm, const void *pos, const double lo[3], double size, double4 *rec,
+                             hipStream_t st) {
     if (dtype == FMM_F64)
-        k_ad_records<double><<<ad_blocks(n, 256), 256, 0, st>>>(n, hoff, lbox, lev, code, perm, (const double *)pos,
-                                                                lo[0], lo[1], lo[2], 1.0 / size, rec);
+        k_ad_records<double><<<ad_blocks(n, 256), 256, 0, st>>>(n, Lf, span, skey, perm, (const double *)pos, lo[0],
+                                                                lo[1], lo[2], 1.0 / size, rec);
     else
-        k_ad_records<float><<<ad_blocks(n, 256), 256, 0, st>>>(n, hoff, lbox, lev, code, perm, (const float *)pos,
-                                                               lo[0], lo[1], lo[2], 1.0 / size, rec);
+        k_ad_records<float><<<ad_blocks(n, 256), 256, 0, st>>>(n, Lf, span, skey, perm, (const float *)pos, lo[0],
+                                                               lo[1], lo[2], 1.0 / size, rec);
     return hipGetLastError();
 }
 
@@ -1666,9 +1714,9 @@ hipError_t ad_launch_m2l_h(int P, const AdM2LPlan &pl, const uint16_t *Ah, size_
 }
 
 hipError_t ad_launch_class(int64_t box2, int64_t nb, const int *lev, const uint32_t *code, unsigned int *cnt,
-                           const int64_t *goff, unsigned int *fill, int *tgt, hipStream_t st) {
+                           const AdGroupStarts &gs, unsigned int *fill, int *tgt, hipStream_t st) {
     if (nb == 0) return hipSuccess;
-    k_ad_class<<<ad_blocks(nb, 256), 256, 0, st>>>(box2, nb, lev, code, cnt, goff, fill, tgt);
+    k_ad_class<<<ad_blocks(nb, 256), 256, 0, st>>>(box2, nb, lev, code, cnt, gs, fill, tgt);
     return hipGetLastError();
 }
 

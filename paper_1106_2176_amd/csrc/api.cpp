@@ -64,7 +64,7 @@ struct Buf {
 // and freeing pinned memory costs more than the rest of a small tree's life
 // (the free waits for the device), so a destroyed tree leaves its kit for the
 // next one on its device; at most kKits wait, the others are freed.
-constexpr int kAdHostWords = 128;  // adaptive build: 4 totals + 8 groups per level 2..10
+constexpr int kAdHostWords = 128;  // adaptive build: 3 totals + 8 groups per level 2..10
 struct HostKit {
     int dev = 0;
     unsigned int *words = nullptr;      // pinned, coherent: 4 counters, then kAdHostWords
@@ -428,14 +428,14 @@ struct AdTree {
     int64_t nbox = 0, nleaf = 0, nvbox = 0;  // nvbox: boxes of levels >= 2
     int64_t off[FMM_MAX_LEVEL + 2] = {};      // first box of each level, off[depth + 1] = nbox
     int64_t nlist[3] = {};                    // items of U, W, X
-    int64_t goff[8 * FMM_MAX_LEVEL + 1] = {}; // first target of each (level, class) group
     AdM2LPlan plan{};                         // mixed form
     FoldPlan fold{};                          // FP64 form
     uint32_t *hbuf = nullptr;                 // the kit's words for the build's counts
-    Buf code, ps, pe, parent, child, leaf, cmask, nchild, coff, lev, col, vidx, cnts, offs, iu, iw, ix,
-        is_head, head, hoff, lbox, lstart, llev, tgt, ccnt, goffd, offd, ucnt, uoff, units, s27, units_m;
+    Buf code, ps, pe, parent, child, leaf, lev, col, vidx, cnts, offs, iu, iw, ix, lbox, lstart, llev, tgt, ccnt,
+        ucnt, uoff, units, s27, units_m;
     Buf skey, cstart, ks_a, ks_b, ks_v, ks_h;  // the key sort: sorted keys, coarse starts, scratch
-    Buf area[3];            // hold the buffers above: by particles and box bound, by boxes, by list items
+    Buf span, bcnt, bbase;  // the boxes each particle heads, their counts per (level, block), scanned
+    Buf area[3];            // hold the buffers above: by particles, by boxes, by list items
     int64_t max_units = 0;  // bound of the P2P work units (their count stays on the device)
 };
 
@@ -873,12 +873,11 @@ template <typename T>
 T *bp(const Buf &b) { return (T *)b.p; }
 
 // Build of an adaptive tree: keys and the counting sort at the finest level
-// Lf = max_level; the boxes level by level (a box over leaf_max below Lf is
-// split, its non-empty children appended in Morton order; one host read of
-// the child count per level); then the levels, colleagues and V slots, the
-// U/W/X counts and the leaf heads, one host read of their totals and of the
-// M2L group sizes, and the lists, the leaf list, the leaf-relative records
-// and the grouped M2L targets.
+// Lf = max_level, the box levels of every particle and one host read of the
+// boxes per level (the records, relative to the leaves, run meanwhile); the
+// boxes, the leaf list and the colleagues; the U/W/X counts and one host read
+// of their totals and of the M2L group sizes (the V slots run meanwhile); the
+// lists, the P2P units and the grouped M2L targets.
 fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos, hipStream_t st) {
     const fmm_config &c = t->cfg;
     const int Lf = c.max_level;
@@ -892,29 +891,18 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     int cl = 0;
     while (cl < std::min(Lf, 7) && ((int64_t)1 << (3 * cl)) < n) ++cl;
     const int64_t nc = (int64_t)1 << (3 * cl), hw = key_sort_hist_words(n);
-    // the boxes of a level l >= 1 are non-empty children of split boxes of
-    // level l - 1, which are disjoint and hold more than leaf_max each
-    int64_t bound = 0;
-    for (int l = 0; l <= Lf; ++l) {
-        int64_t b = std::min<int64_t>((int64_t)1 << (3 * l), n);
-        if (l > 0) b = std::min<int64_t>(b, 8 * (n / ((int64_t)c.leaf_max + 1)));
-        bound += b;
-    }
+    const int64_t rows = (Lf + 2) * ad_box_blocks(n);
     const size_t u4 = sizeof(uint32_t);
     CHK(place(t, a->area[0],
               {{&t->key10, u4 * n}, {&t->counters, 4 * u4}, {&t->perm, u4 * n}, {&t->xyz64, sizeof(double4) * n},
-               {&t->scan, u4 * scan_scratch_words(bound + 1)}, {&a->skey, u4 * n}, {&a->cstart, u4 * (nc + 1)},
+               {&t->scan, u4 * scan_scratch_words(rows + 1)}, {&a->skey, u4 * n}, {&a->cstart, u4 * (nc + 1)},
                {&a->ks_a, u4 * n}, {&a->ks_b, u4 * n}, {&a->ks_v, u4 * n},
-               {&a->ks_h, u4 * (2 * hw + 1 + scan_scratch_words(hw))}, {&a->code, u4 * bound}, {&a->ps, u4 * bound},
-               {&a->pe, u4 * bound}, {&a->parent, u4 * bound}, {&a->child, 8 * u4 * bound},
-               {&a->leaf, (size_t)bound + 4},  // read back as whole words by the export
-               {&a->cmask, (size_t)bound}, {&a->nchild, u4 * bound}, {&a->coff, u4 * (bound + 1)}},
+               {&a->ks_h, u4 * (2 * hw + 1 + scan_scratch_words(hw))}, {&a->span, (size_t)n},
+               {&a->bcnt, u4 * rows}, {&a->bbase, u4 * (rows + 1)}},
               st));
-    unsigned int *dc = bp<unsigned int>(t->counters);
-    uint32_t *code = bp<uint32_t>(a->code), *ps = bp<uint32_t>(a->ps), *pe = bp<uint32_t>(a->pe);
-    int *parent = bp<int>(a->parent), *child = bp<int>(a->child);
-    uint8_t *leaf = bp<uint8_t>(a->leaf);
-    uint32_t *scan = bp<uint32_t>(t->scan);
+    unsigned int *dc = bp<unsigned int>(t->counters), *hdev = t->kit.words_dev + 4;  // of hbuf, for kernels
+    uint32_t *scan = bp<uint32_t>(t->scan), *skey = bp<uint32_t>(a->skey), *perm = bp<uint32_t>(t->perm);
+    uint8_t *span = bp<uint8_t>(a->span);
     KeySortWork ksw;
     ksw.keys_a = bp<uint32_t>(a->ks_a);
     ksw.keys_b = bp<uint32_t>(a->ks_b);
@@ -922,41 +910,23 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     ksw.hist = bp<uint32_t>(a->ks_h);
     ksw.off = ksw.hist + hw;
     ksw.scan = ksw.off + hw + 1;
-    const KeyIndex ki{bp<uint32_t>(a->cstart), bp<uint32_t>(a->skey), Lf, cl};
-    auto host_read = [&]() -> fmm_status {
-        HIPCHK(hipEventRecord(t->kit.ev, st));
-        HIPCHK(hipEventSynchronize(t->kit.ev));
-        return FMM_OK;
-    };
+    const KeyIndex ki{bp<uint32_t>(a->cstart), skey, Lf, cl};
     HIPCHK(launch_keys(n, dtype, pos, c.box_lo, c.box_size, Lf, bp<uint32_t>(t->key10), nullptr, nullptr, dc, st));
-    HIPCHK(launch_key_sort(n, Lf, bp<uint32_t>(t->key10), ksw, bp<uint32_t>(t->perm), bp<uint32_t>(a->skey), st));
-    HIPCHK(launch_records(n, Lf, bp<uint32_t>(t->perm), bp<uint32_t>(t->key10), dtype, pos, c.box_lo, c.box_size,
-                          bp<double4>(t->xyz64), st));
-    HIPCHK(launch_key_starts(n, Lf, cl, bp<uint32_t>(a->skey), bp<uint32_t>(a->cstart), st));
-    a->off[0] = 0;
-    a->off[1] = 1;
-    HIPCHK(ad_launch_root((uint32_t)n, code, ps, pe, parent, st));
-    int l = 0;
-    for (;; ++l) {
-        const int64_t b0 = a->off[l], nb = a->off[l + 1] - a->off[l];
-        HIPCHK(ad_launch_count(b0, nb, l, Lf, c.leaf_max, code, ps, pe, ki, leaf, bp<uint32_t>(a->nchild),
-                               bp<uint8_t>(a->cmask), st));
-        HIPCHK(launch_scan(nb, bp<uint32_t>(a->nchild), bp<uint32_t>(a->coff), scan, st));
-        HIPCHK(ad_launch_children(b0, nb, l, Lf, a->off[l + 1], ki, bp<uint32_t>(a->coff),
-                                  bp<uint8_t>(a->cmask), code, ps, pe, parent, child, st));
-        HIPCHK(hipMemcpyAsync(a->hbuf, bp<uint32_t>(a->coff) + nb, u4, hipMemcpyDeviceToHost, st));
-        if (l == 0) HIPCHK(hipMemcpyAsync(a->hbuf + 1, dc, u4, hipMemcpyDeviceToHost, st));
-        CHK(host_read());
-        if (l == 0 && a->hbuf[1] != 0)
-            return fail(FMM_EDOMAIN, std::to_string(a->hbuf[1]) + " positions outside the root cube or not finite");
-        const int64_t kids = a->hbuf[0];
-        if (kids == 0) break;
-        if (a->off[l + 1] + kids > bound) return fail(FMM_EDEVICE, "internal: box count over its bound");
-        a->off[l + 2] = a->off[l + 1] + kids;
-    }
-    const int nlev = l + 1;
-    const int64_t nbox = a->off[nlev];
-    a->depth = l;
+    HIPCHK(launch_key_sort(n, Lf, bp<uint32_t>(t->key10), ksw, perm, skey, st));
+    HIPCHK(launch_key_starts(n, Lf, cl, skey, bp<uint32_t>(a->cstart), st));
+    HIPCHK(ad_launch_spans(n, c.leaf_max, ki, span, bp<uint32_t>(a->bcnt), bp<uint32_t>(a->bbase), scan, dc, hdev,
+                           st));
+    HIPCHK(hipEventRecord(t->kit.ev, st));
+    HIPCHK(ad_launch_records(n, dtype, Lf, span, skey, perm, pos, c.box_lo, c.box_size, bp<double4>(t->xyz64), st));
+    HIPCHK(hipEventSynchronize(t->kit.ev));
+    if (a->hbuf[Lf + 3] != 0)
+        return fail(FMM_EDOMAIN, std::to_string(a->hbuf[Lf + 3]) + " positions outside the root cube or not finite");
+    const int64_t nbox = a->hbuf[Lf + 1];
+    a->nleaf = a->hbuf[Lf + 2] - nbox;
+    int nlev = 0;  // levels with boxes
+    for (; nlev <= Lf && a->hbuf[nlev] < nbox; ++nlev) a->off[nlev] = a->hbuf[nlev];
+    a->off[nlev] = nbox;
+    a->depth = nlev - 1;
     a->nbox = nbox;
     a->nvbox = nlev > 2 ? nbox - a->off[2] : 0;
     if (!t->ops) CHK(build_ops(c.p, &t->ops));
@@ -965,58 +935,52 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     const bool f64 = is_f64_form(t);
     const int ngrp = f64 ? 0 : 8 * std::max(nlev - 2, 0);
     CHK(place(t, a->area[1],
-              {{&a->lev, u4 * nbox}, {&a->col, 27 * u4 * nbox},
-               {&a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1)},
-               {&a->offd, sizeof(int64_t) * (nlev + 1)}, {&a->cnts, 3 * u4 * n27}, {&a->s27, 3 * u4 * (n27 + 1)},
-               {&a->offs, 3 * u4 * (nbox + 1)}, {&t->scan, u4 * scan_scratch_words(std::max(3 * n27, n) + 1)},
-               {&a->is_head, u4 * n}, {&a->head, u4 * n}, {&a->hoff, u4 * (n + 1)},
-               {&a->ccnt, u4 * std::max(ngrp, 1)}},
+              {{&a->code, u4 * nbox}, {&a->ps, u4 * nbox}, {&a->pe, u4 * nbox}, {&a->parent, u4 * nbox},
+               {&a->child, 8 * u4 * nbox}, {&a->leaf, (size_t)nbox + 4},  // read back as whole words by the export
+               {&a->lev, u4 * nbox}, {&a->col, 27 * u4 * nbox}, {&a->lbox, u4 * a->nleaf},
+               {&a->lstart, u4 * (a->nleaf + 1)}, {&a->llev, (size_t)a->nleaf},
+               {&a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1)}, {&a->cnts, 3 * u4 * n27},
+               {&a->s27, 3 * u4 * (n27 + 1)}, {&a->offs, 3 * u4 * (nbox + 1)},
+               {&t->scan, u4 * scan_scratch_words(3 * n27 + 1)}, {&a->ccnt, u4 * std::max(ngrp, 1)}},
               st));
     scan = bp<uint32_t>(t->scan);
-    int *lev = bp<int>(a->lev), *col = bp<int>(a->col), *vidx = bp<int>(a->vidx);
+    const AdBoxes bx{bp<uint32_t>(a->code), bp<uint32_t>(a->ps), bp<uint32_t>(a->pe),    bp<int>(a->lev),
+                     bp<int>(a->parent),    bp<int>(a->child),   bp<uint8_t>(a->leaf),   bp<int>(a->lbox),
+                     bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev)};
+    uint32_t *code = bx.code, *ps = bx.ps, *pe = bx.pe;
+    int *lev = bx.lev, *parent = bx.parent, *child = bx.child, *col = bp<int>(a->col);
+    uint8_t *leaf = bx.leaf;
     uint32_t *nu = bp<uint32_t>(a->cnts), *nw = nu + n27, *nx = nw + n27;
     // the U, W and X counts (contiguous) in one scan: run k starts at k n27
     uint32_t *su = bp<uint32_t>(a->s27), *sw = su + n27, *sx = sw + n27;
     uint32_t *ou = bp<uint32_t>(a->offs), *ow = ou + nbox + 1, *ox = ow + nbox + 1;
-    HIPCHK(hipMemcpyAsync(a->offd.p, a->off, sizeof(int64_t) * (nlev + 1), hipMemcpyHostToDevice, st));
-    HIPCHK(ad_launch_structure(nbox, nlev, a->off, bp<int64_t>(a->offd), code, parent, child, lev, col,
-                               f64 ? t->ops->fold.cls : t->ops->cls, vidx, st));
+    HIPCHK(ad_launch_boxes(n, nbox, a->nleaf, ki, span, bp<uint32_t>(a->bbase), bx, col, st));
     HIPCHK(ad_launch_lists(nbox, 0, lev, code, parent, col, child, leaf, nu, nw, nx, nullptr, nullptr, nullptr,
                            nullptr, nullptr, nullptr, st));
     HIPCHK(launch_scan(3 * n27, nu, su, scan, st));
-    HIPCHK(ad_launch_box_offsets(nbox, su, ou, ow, ox, st));
-    HIPCHK(launch_zero(bp<uint32_t>(a->is_head), n, st));
-    HIPCHK(ad_launch_heads(nbox, leaf, ps, pe, bp<uint32_t>(a->is_head), bp<int>(a->head), st));
-    HIPCHK(launch_scan(n, bp<uint32_t>(a->is_head), bp<uint32_t>(a->hoff), scan, st));
     if (ngrp) {
         HIPCHK(launch_zero(bp<uint32_t>(a->ccnt), ngrp, st));
-        HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, bp<unsigned int>(a->ccnt), nullptr, nullptr,
+        HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, bp<unsigned int>(a->ccnt), AdGroupStarts{}, nullptr,
                                nullptr, st));
-        HIPCHK(hipMemcpyAsync(a->hbuf + 4, a->ccnt.p, u4 * ngrp, hipMemcpyDeviceToHost, st));
     }
-    HIPCHK(hipMemcpyAsync(a->hbuf, ou + nbox, u4, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(a->hbuf + 1, ow + nbox, u4, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(a->hbuf + 2, ox + nbox, u4, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(a->hbuf + 3, bp<uint32_t>(a->hoff) + n, u4, hipMemcpyDeviceToHost, st));
-    CHK(host_read());
+    HIPCHK(ad_launch_box_offsets(nbox, su, ou, ow, ox, ngrp, bp<unsigned int>(a->ccnt), hdev, st));
+    HIPCHK(hipEventRecord(t->kit.ev, st));
+    HIPCHK(ad_launch_vslots(a->off[std::min(nlev, 2)], a->nvbox, code, parent, col, child,
+                            f64 ? t->ops->fold.cls : t->ops->cls, bp<int>(a->vidx), st));
+    HIPCHK(hipEventSynchronize(t->kit.ev));
     for (int k = 0; k < 3; ++k) a->nlist[k] = a->hbuf[k];
-    a->nleaf = a->hbuf[3];
     // P2P work units: at most one per leaf plus one per 64 particles
     a->max_units = a->nleaf + n / 64;
     CHK(place(t, a->area[2],
               {{&a->iu, u4 * a->nlist[0]}, {&a->iw, u4 * a->nlist[1]}, {&a->ix, u4 * a->nlist[2]},
-               {&a->lbox, u4 * a->nleaf}, {&a->lstart, u4 * (a->nleaf + 1)}, {&a->llev, (size_t)a->nleaf},
                {&a->ucnt, u4 * 2 * kAdUnitClasses * a->nleaf}, {&a->uoff, u4 * (2 * kAdUnitClasses * a->nleaf + 1)},
                {&a->units, sizeof(int2) * a->max_units}, {&a->units_m, sizeof(int2) * a->max_units},
-               {&a->tgt, ngrp ? u4 * a->nvbox : 0}, {&a->goffd, sizeof(int64_t) * (ngrp + 1)}},
+               {&a->tgt, ngrp ? u4 * a->nvbox : 0}},
               st));
     HIPCHK(ad_launch_lists(nbox, 1, lev, code, parent, col, child, leaf, nu, nw, nx, su, sw, sx, bp<int>(a->iu),
                            bp<int>(a->iw), bp<int>(a->ix), st));
     HIPCHK(launch_zero(dc + 3, 1, st));
-    HIPCHK(ad_launch_leaflist(n, a->nleaf, bp<uint32_t>(a->is_head), bp<uint32_t>(a->hoff), bp<int>(a->head), ps,
-                              bp<int>(a->lbox), bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev), lev, dc + 3, st));
-    HIPCHK(ad_launch_records(n, dtype, bp<uint32_t>(a->hoff), bp<int>(a->lbox), lev, code, bp<uint32_t>(t->perm),
-                             pos, c.box_lo, c.box_size, bp<double4>(t->xyz64), st));
+    HIPCHK(ad_launch_leafmax(a->nleaf, bx.lstart, dc + 3, st));
     // work units, heaviest first: one run of nleaf counts per weight class
     // and order (P2P over U, M2P over W), and one scan
     HIPCHK(ad_launch_units(a->nleaf, 0, bp<uint32_t>(a->lstart), bp<int>(a->lbox), ou, ow, bp<int>(a->iu), ps, pe,
@@ -1027,10 +991,11 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                            st));
     // M2L targets grouped by (level, class), tiles of 128 targets per block
     a->plan = AdM2LPlan{};
+    AdGroupStarts gs{};
     int64_t at = 0;
     for (int g = 0; g < ngrp; ++g) {
-        a->goff[g] = at;
-        const int64_t cnt = a->hbuf[4 + g];
+        gs.at[g] = at;
+        const int64_t cnt = a->hbuf[3 + g];
         if (cnt) {
             AdM2LGroup &e = a->plan.grp[a->plan.ngroups++];
             e.unit0 = a->plan.units;
@@ -1042,7 +1007,6 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
         }
         at += cnt;
     }
-    a->goff[ngrp] = at;
     // K-split so that the launch has about four blocks per compute unit
     a->plan.nsplit = a->plan.units ? (int)std::min<int64_t>(8, std::max<int64_t>(1, (4 * t->ncu + a->plan.units - 1) /
                                                                                          a->plan.units))
@@ -1061,9 +1025,8 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
         a->fold = fold_plan(c.p, (a->nvbox + tt - 1) / tt, t->ncu, most > pack ? most - pack : 0);
     }
     if (ngrp) {
-        HIPCHK(hipMemcpyAsync(a->goffd.p, a->goff, sizeof(int64_t) * (ngrp + 1), hipMemcpyHostToDevice, st));
         HIPCHK(launch_zero(bp<uint32_t>(a->ccnt), ngrp, st));
-        HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, nullptr, bp<int64_t>(a->goffd),
+        HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, nullptr, gs,
                                bp<unsigned int>(a->ccnt), bp<int>(a->tgt), st));
     }
     t->L = a->depth;

@@ -44,9 +44,6 @@ struct KeySortWork {
 int64_t key_sort_hist_words(int64_t n);
 hipError_t launch_key_sort(int64_t n, int level, const uint32_t *key10, const KeySortWork &w, uint32_t *perm,
                            uint32_t *skey, hipStream_t st);
-// FP64 leaf-relative records at `level` in sorted order
-hipError_t launch_records(int64_t n, int level, const uint32_t *perm, const uint32_t *key10, int dtype,
-                          const void *pos, const double lo[3], double size, double4 *xyz64, hipStream_t st);
 // cstart[x], x in [0, 8^cl]: the first sorted position whose key at level
 // cl is >= x, from the keys at `level` >= cl sorted (skey)
 hipError_t launch_key_starts(int64_t n, int level, int cl, const uint32_t *skey, uint32_t *cstart, hipStream_t st);
@@ -115,24 +112,37 @@ __host__ __device__ constexpr int tz_size(int P) { return tz_off(P, P, 0); }
 hipError_t launch_m2l_rot(int P, int L, void *const *B, void *const *Lc, const double *rot,
                           const double *tz, const int2 *cls, hipStream_t st);
 
-// adaptive.hip: the adaptive octree (FP64 form); see the file's header for
-// the layout.  Build steps (per level, host-driven) and list construction:
-hipError_t ad_launch_root(uint32_t n, uint32_t *code, uint32_t *ps, uint32_t *pe, int *parent, hipStream_t st);
+// adaptive.hip: the adaptive octree; see the file's header for the layout.
 // the sorted keys of the finest level Lf and the first position of each
 // key of level cl <= Lf (cstart[8^cl + 1]), for the box ranges
 struct KeyIndex {
     const uint32_t *cstart, *skey;
     int Lf, cl;
 };
-hipError_t ad_launch_count(int64_t b0, int64_t nb, int l, int Lf, int leaf_max, const uint32_t *code,
-                           const uint32_t *ps, const uint32_t *pe, const KeyIndex &ki, uint8_t *leaf,
-                           uint32_t *nchild, uint8_t *cmask, hipStream_t st);
-hipError_t ad_launch_children(int64_t b0, int64_t nb, int l, int Lf, int64_t next0, const KeyIndex &ki,
-                              const uint32_t *coff, const uint8_t *cmask, uint32_t *code, uint32_t *ps,
-                              uint32_t *pe, int *parent, int *child, hipStream_t st);
-hipError_t ad_launch_structure(int64_t nbox, int nlev, const int64_t *off_host, const int64_t *off_dev,
-                               const uint32_t *code, const int *parent, const int *child, int *lev, int *col,
-                               const int2 *cls, int *vidx, hipStream_t st);
+// boxes by id and leaves by index, in particle order
+struct AdBoxes {
+    uint32_t *code, *ps, *pe;  // Morton code at the box's level; its particles [ps, pe)
+    int *lev, *parent, *child; // child[8 g + octant], -1: absent
+    uint8_t *leaf;
+    int *lbox;                 // leaf -> box
+    uint32_t *lstart;          // [nleaf + 1]
+    uint8_t *llev;
+};
+constexpr int kAdBoxBlock = 1024;  // particles per block of the box counts
+int64_t ad_box_blocks(int64_t n);
+// Box levels of every particle (span[n]: the coarsest level whose box it
+// heads, above all if none, in the low four bits; the level of its leaf in the
+// high four), the boxes and leaves headed per (row, block) and their scan
+// (cnt, base[(Lf + 2) ad_box_blocks(n) + 1]); host[0..Lf + 1] = first box of
+// each level and the box count, host[Lf + 2] = boxes + leaves, host[Lf + 3] =
+// *nbad.
+hipError_t ad_launch_spans(int64_t n, int leaf_max, const KeyIndex &ki, uint8_t *span, uint32_t *cnt, uint32_t *base,
+                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, hipStream_t st);
+// the boxes, the leaf list and the colleagues (col[27 nbox])
+hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyIndex &ki, const uint8_t *span,
+                           const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st);
+hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const uint32_t *code, const int *parent, const int *col,
+                            const int *child, const int2 *cls, int *vidx, hipStream_t st);
 // one thread per (box, direction): pass 0 counts [27 nbox] each, pass 1
 // fills at the scanned per-(box, direction) offsets
 hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_t *code, const int *parent,
@@ -140,24 +150,25 @@ hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_
                            uint32_t *nx, const uint32_t *ou, const uint32_t *ow, const uint32_t *ox, int *iu,
                            int *iw, int *ix, hipStream_t st);
 // per-box list offsets ou/ow/ox [nbox + 1] from the three per-(box,
-// direction) scans stored one after another, each 27 nbox + 1 long
+// direction) scans stored one after another, each 27 nbox + 1 long; host[0..2]
+// = the list lengths, host[3..] = ccnt[ngrp]
 hipError_t ad_launch_box_offsets(int64_t nbox, const uint32_t *s27, uint32_t *ou, uint32_t *ow, uint32_t *ox,
-                                 hipStream_t st);
-hipError_t ad_launch_heads(int64_t nbox, const uint8_t *leaf, const uint32_t *ps, const uint32_t *pe,
-                           uint32_t *is_head, int *head, hipStream_t st);
-// leaves in particle order, and the fullest leaf's count into *mx
-hipError_t ad_launch_leaflist(int64_t n, int64_t nleaf, const uint32_t *is_head, const uint32_t *hoff,
-                              const int *head, const uint32_t *ps, int *lbox, uint32_t *lstart, uint8_t *llev,
-                              const int *lev, unsigned int *mx, hipStream_t st);
+                                 int ngrp, const unsigned int *ccnt, unsigned int *host, hipStream_t st);
+// the fullest leaf's count into *mx
+hipError_t ad_launch_leafmax(int64_t nleaf, const uint32_t *lstart, unsigned int *mx, hipStream_t st);
 // out[4] (zeroed): ordered P2P pairs incl. self, V entries, W and X (particle, box) pairs
 hipError_t ad_launch_counts(int64_t nbox, int64_t box2, const uint8_t *leaf, const uint32_t *ps, const uint32_t *pe,
                             const uint32_t *ou, const int *iu, const uint32_t *ow, const uint32_t *ox, const int *ix,
                             const int *vidx, unsigned long long *out, hipStream_t st);
-hipError_t ad_launch_records(int64_t n, int dtype, const uint32_t *hoff, const int *lbox, const int *lev,
-                             const uint32_t *code, const uint32_t *perm, const void *pos, const double lo[3],
-                             double size, double4 *rec, hipStream_t st);
+hipError_t ad_launch_records(int64_t n, int dtype, int Lf, const uint8_t *span, const uint32_t *skey,
+                             const uint32_t *perm, const void *pos, const double lo[3], double size, double4 *rec,
+                             hipStream_t st);
+// first target of each (level, class) group
+struct AdGroupStarts {
+    int64_t at[8 * FMM_MAX_LEVEL + 1];
+};
 hipError_t ad_launch_class(int64_t box2, int64_t nb, const int *lev, const uint32_t *code, unsigned int *cnt,
-                           const int64_t *goff, unsigned int *fill, int *tgt, hipStream_t st);
+                           const AdGroupStarts &gs, unsigned int *fill, int *tgt, hipStream_t st);
 // M2L targets: groups (level >= 2, class) of the target list, tiles of 128
 struct AdM2LGroup {
     int64_t unit0;  // first block of the group

@@ -366,26 +366,6 @@ __global__ void k_iota(int64_t n, uint32_t *__restrict__ v, uint32_t *__restrict
     }
 }
 
-// Sorted records: for sorted position d the particle perm[d] relative to its
-// leaf centre in units of the leaf width, u = s 2^L - (i + 1/2), computed in
-// FP64 as the fix-up does.
-template <typename T>
-__global__ void k_records(int64_t n, int L, const uint32_t *__restrict__ perm, const uint32_t *__restrict__ key10,
-                          const T *__restrict__ pos, double lo0, double lo1, double lo2, double size,
-                          double4 *__restrict__ xyz64) {
-    const int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= n) return;
-    const uint32_t me = perm[d];
-    const uint32_t leaf = key10[me] >> (3 * (10 - L));
-    const double scale = (double)(1u << L);
-    const double bx = (double)compact3(leaf) + 0.5, by = (double)compact3(leaf >> 1) + 0.5,
-                 bz = (double)compact3(leaf >> 2) + 0.5;
-    const double ux = ((double)pos[3 * (size_t)me] - lo0) / size * scale - bx;
-    const double uy = ((double)pos[3 * (size_t)me + 1] - lo1) / size * scale - by;
-    const double uz = ((double)pos[3 * (size_t)me + 2] - lo2) / size * scale - bz;
-    xyz64[d] = make_double4(ux, uy, uz, 0.0);
-}
-
 // First sorted position of every key at level cl (cstart[x], x in
 // [0, 8^cl]) from the keys at level L >= cl sorted: a binary search per x
 // (an empty stretch of keys costs no thread more than another).
@@ -557,17 +537,6 @@ hipError_t launch_key_sort(int64_t n, int level, const uint32_t *key10, const Ke
         kin = kout;
         vin = vout;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_records(int64_t n, int level, const uint32_t *perm, const uint32_t *key10, int dtype,
-                          const void *pos, const double lo[3], double size, double4 *xyz64, hipStream_t st) {
-    if (dtype == FMM_F64)
-        k_records<double><<<nblk(n, 256), 256, 0, st>>>(n, level, perm, key10, (const double *)pos, lo[0], lo[1],
-                                                        lo[2], size, xyz64);
-    else
-        k_records<float><<<nblk(n, 256), 256, 0, st>>>(n, level, perm, key10, (const float *)pos, lo[0], lo[1],
-                                                       lo[2], size, xyz64);
     return hipGetLastError();
 }
 
