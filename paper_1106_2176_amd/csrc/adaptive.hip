@@ -186,10 +186,12 @@ __global__ __launch_bounds__(64 * kAdBoxWaves) void k_ad_spans(int64_t n, int64_
 }
 
 // The scanned counts' row starts (the first box of every level, then nbox and
-// the total of boxes and leaves) and the count of bad positions, for the host.
+// the total of boxes and leaves) and the count of bad positions, for the host;
+// the counts of split boxes cleared.
 __global__ void k_ad_sizes(int64_t nblk, int Lf, const uint32_t *__restrict__ base, const unsigned int *nbad,
-                           unsigned int *__restrict__ host) {
+                           unsigned int *__restrict__ host, unsigned int *__restrict__ nsplit) {
     const int r = threadIdx.x;
+    if (r <= Lf) nsplit[r] = 0u;
     if (r <= Lf + 2) host[r] = base[r * nblk];
     if (r == Lf + 3) host[r] = *nbad;
 }
@@ -267,13 +269,33 @@ __global__ __launch_bounds__(64 * kAdBoxWaves) void k_ad_boxes(int64_t n, int64_
 }
 
 // The end of every box's range, and its children: the boxes from the first
-// child on (found by k_ad_boxes) whose parent it is, at most eight.
-__global__ __launch_bounds__(256) void k_ad_links(int64_t nbox, const KeyIndex ki, AdBoxes bx) {
+// child on (found by k_ad_boxes) whose parent it is, at most eight; the split
+// boxes of each level listed from the level's first box on (in no fixed
+// order: what is computed for one does not depend on its place).
+__global__ __launch_bounds__(256) void k_ad_links(int64_t nbox, int64_t nblk, const KeyIndex ki,
+                                                  const uint32_t *__restrict__ base, AdBoxes bx) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int l = g < nbox ? bx.lev[g] : -1;
+    int64_t j = nbox;
+    if (g < nbox) {
+        bx.pe[g] = key_start(ki, ((uint64_t)bx.code[g] + 1) << (3 * (ki.Lf - l)));
+        if (bx.child[8 * g] >= 0) j = bx.child[8 * g];
+    }
+    const bool split = j < nbox;
+    const uint64_t m = __ballot(split);
+    if (split) {
+        const int lead = __ffsll((unsigned long long)m) - 1;
+        uint32_t at = 0;
+        if (__ballot(split && l == __shfl(l, lead)) == m) {  // one level: one atomic for the wave
+            if (lane == lead) at = atomicAdd(&bx.nsplit[l], (unsigned int)__popcll(m));
+            at = __shfl(at, lead) + (uint32_t)__popcll(m & (((uint64_t)1 << lane) - 1));
+        } else {
+            at = atomicAdd(&bx.nsplit[l], 1u);
+        }
+        bx.split[base[l * nblk] + at] = (int)g;
+    }
     if (g >= nbox) return;
-    bx.pe[g] = key_start(ki, ((uint64_t)bx.code[g] + 1) << (3 * (ki.Lf - bx.lev[g])));
-    int64_t j = bx.child[8 * g];
-    if (j < 0) j = nbox;
     for (uint32_t c = 0; c < 8; ++c) {
         int r = -1;
         if (j < nbox && bx.parent[j] == (int)g && (bx.code[j] & 7u) == c) r = (int)j++;
@@ -419,13 +441,15 @@ __global__ void k_ad_lists(int64_t nbox, int pass, const int *__restrict__ lev, 
 }
 
 // Per-box list offsets from the per-(box, direction) scans: box g starts at
-// its direction 0 (g = nbox: the totals, also for the host, with the ngrp
-// group counts of the M2L targets).
+// its direction 0 (g = nbox: the totals, also for the host, with the split
+// boxes per level and the ngrp group counts of the M2L targets).
 __global__ void k_ad_box_offsets(int64_t nbox, const uint32_t *__restrict__ s27, uint32_t *__restrict__ ou,
-                                 uint32_t *__restrict__ ow, uint32_t *__restrict__ ox, int ngrp,
+                                 uint32_t *__restrict__ ow, uint32_t *__restrict__ ox, int nlev,
+                                 const unsigned int *__restrict__ nsplit, int ngrp,
                                  const unsigned int *__restrict__ ccnt, unsigned int *__restrict__ host) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < ngrp) host[3 + g] = ccnt[g];
+    if (g < nlev) host[3 + g] = nsplit[g];
+    if (g < ngrp) host[3 + nlev + g] = ccnt[g];
     if (g > nbox) return;
     const int64_t m = 27 * nbox;  // one scan of the U, W and X counts: run k starts at s27[k m]
     const uint32_t u = s27[27 * g], w = s27[m + 27 * g] - s27[m], x = s27[2 * m + 27 * g] - s27[2 * m];
@@ -655,89 +679,115 @@ __global__ __launch_bounds__(64) void k_ad_p2m(const int *__restrict__ lbox, con
     }
 }
 
-// M2M for the split boxes of one level: mu(g) = sum_c A_c mu(child c)
-// (tab [8][p^2][p^2] input-major, [c][in][out]).  A block takes BX
-// consecutive boxes of the level, so that each table entry read from L2
-// serves BX boxes (one box a block read the whole 8 p^4 table per box); its
-// threads are (output o, K part kg), KG parts of the p^2 inputs per output,
-// whose partial sums are joined through LDS in kg order.
-template <int P>
-__global__ __launch_bounds__(256) void k_ad_m2m(int64_t b0, int64_t nb, const uint8_t *__restrict__ leaf,
-                                                const int *__restrict__ child, const double *__restrict__ tab,
-                                                double *__restrict__ M) {
-    constexpr int P2 = P * P, S = coef_stride(P);
-    constexpr int KG = P2 > 128 ? 1 : (P2 > 64 ? 2 : 4);
-    constexpr int BX0 = 4096 / (8 * P2), BX = BX0 < 1 ? 1 : (BX0 > 8 ? 8 : BX0);
-    constexpr int KL = (P2 + KG - 1) / KG;  // inputs per part
-    __shared__ double in[BX][8][P2];
-    __shared__ double part[KG][BX][P2];
-    __shared__ int has[BX][8];
-    const int64_t g0 = b0 + (int64_t)blockIdx.x * BX;
-    const int nbx = (int)min((int64_t)BX, b0 + nb - g0);
-    const int tid = threadIdx.x;
-    for (int i = tid; i < BX * 8 * P2; i += 256) {
-        const int bx = i / (8 * P2), r = i - bx * 8 * P2, c = r / P2, k = r - c * P2;
-        int ch = -1;
-        if (bx < nbx && !leaf[g0 + bx]) ch = child[8 * (g0 + bx) + c];
-        in[bx][c][k] = ch >= 0 ? M[(size_t)ch * S + k] : 0.0;
-    }
-    for (int i = tid; i < BX * 8; i += 256) {
-        const int bx = i >> 3, c = i & 7;
-        has[bx][c] = bx < nbx && !leaf[g0 + bx] && child[8 * (g0 + bx) + c] >= 0;
-    }
-    __syncthreads();
-    const int o = tid % P2, kg = tid / P2;
-    if (kg < KG) {
-        double v[BX];
+// The vertical translations on the matrix cores (v_mfma_f64_16x16x4_f64): a
+// block takes 16 split boxes of a level from the level's list as columns and
+// two tiles of 16 rows, and its eight waves take one child octant each.  A
+// (tab [8][p^2][p^2] input-major, [c][in][out]) and B are read from L2,
+// sixteen K steps in flight.  The list matters because about one box in five
+// is split, in clusters (64 boxes of the level to a block: 110 and 150 us
+// below instead of 65 and 90).  Bound by the latency of a chain of four loads,
+// level after level, so a block takes few row tiles and many K steps at once
+// (four tiles and four steps: 85 and 130 us).
+// 1e6 clustered particles, p = 8, eight levels: 195 us (M2M) and 139 us (L2L)
+// with one to eight boxes a block on the vector units, now 65 and 90 us.
+constexpr int kVertTiles = 2;  // row tiles per block
+__host__ __device__ constexpr int vert_tiles(int rows) {
+    return (rows + 15) / 16 < kVertTiles ? (rows + 15) / 16 : kVertTiles;
+}
+
+// NT tiles of A b added to acc, K = p^2: ap[i] at the lane's row of tile i
+// (clamped into the table), b at the lane's column (any row of the array
+// where not valid: it counts as zero, after the load, so that no load waits
+// on a branch).
+template <int P, int NT>
+__device__ __forceinline__ void ad_vert_tiles(const double *const *ap, const double *__restrict__ b, bool valid, int q,
+                                              f64x4 *acc) {
+    constexpr int P2 = P * P, KS = (P2 + 3) / 4, U = KS < 16 ? KS : 16;
+#pragma unroll 1
+    for (int s0 = 0; s0 < KS; s0 += U) {
+        double av[U][NT], bv[U];
 #pragma unroll
-        for (int bx = 0; bx < BX; ++bx) v[bx] = 0.0;
-        const int k0 = kg * KL, k1 = min(P2, k0 + KL);
-        for (int c = 0; c < 8; ++c) {
-            bool any = false;
+        for (int u = 0; u < U; ++u) {
+            const int kc = min(4 * (s0 + u) + q, P2 - 1);
+            bv[u] = b[kc];
 #pragma unroll
-            for (int bx = 0; bx < BX; ++bx) any |= has[bx][c] != 0;
-            if (!any) continue;
-            const double *tc = tab + (size_t)c * P2 * P2 + o;
-            for (int k = k0; k < k1; ++k) {
-                const double a = tc[(size_t)k * P2];
-#pragma unroll
-                for (int bx = 0; bx < BX; ++bx) v[bx] = __builtin_fma(a, in[bx][c][k], v[bx]);
-            }
+            for (int i = 0; i < NT; ++i) av[u][i] = ap[i][kc * P2];
         }
+        // the loads of a batch stay together: the scheduler would put each
+        // next to its product, a round trip to L2 per K step
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int bx = 0; bx < BX; ++bx) part[kg][bx][o] = v[bx];
-    }
-    __syncthreads();
-    for (int i = tid; i < BX * S; i += 256) {
-        const int bx = i / S, oo = i - bx * S;
-        if (bx >= nbx || leaf[g0 + bx]) continue;
-        double v = 0.0;
-        if (oo < P2)
+        for (int u = 0; u < U; ++u) {
+            const double v = valid && 4 * (s0 + u) + q < P2 ? bv[u] : 0.0;
 #pragma unroll
-            for (int q = 0; q < KG; ++q) v += part[q][bx][oo];
-        M[(size_t)(g0 + bx) * S + oo] = v;
+            for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u][i], v, acc[i], 0, 0, 0);
+        }
     }
 }
 
-// L2L into the boxes of one level (>= 3): ell(g) += B_c ell(parent)
+// M2M into the split boxes of one level (list[cnt]): mu(g) = sum_c A_c
+// mu(child c), the eight octants' tiles joined through LDS in octant order.
 template <int P>
-__global__ __launch_bounds__(256) void k_ad_l2l(int64_t b0, const uint32_t *__restrict__ code,
-                                                const int *__restrict__ parent, const double *__restrict__ tab,
-                                                double *__restrict__ Lc) {
-    constexpr int P2 = P * P, S = coef_stride(P);
-    __shared__ double in[P2];
-    const int64_t g = b0 + blockIdx.x;
-    const int pa = parent[g];
-    for (int k = threadIdx.x; k < P2; k += 256) in[k] = Lc[(size_t)pa * S + k];
-    __syncthreads();
-    const uint32_t cd = code[g];
-    const int c = (int)(cd & 7u);  // the child octant: bit 0 x, 1 y, 2 z of the Morton code
-    for (int o = threadIdx.x; o < P2; o += 256) {
-        double v = 0.0;
-        const double *tc = tab + (size_t)c * P2 * P2 + o;
-        for (int k = 0; k < P2; ++k) v += tc[(size_t)k * P2] * in[k];
-        Lc[(size_t)g * S + o] += v;
+__global__ __launch_bounds__(512) void k_ad_m2m(int cnt, const int *__restrict__ list, const int *__restrict__ child,
+                                                const double *__restrict__ tab, double *__restrict__ M) {
+    constexpr int P2 = P * P, S = coef_stride(P), NT = vert_tiles(S);
+    __shared__ double red[8][4][64];
+    const int lane = threadIdx.x & 63, c = threadIdx.x >> 6, q = lane >> 4, col = lane & 15;
+    const int r0 = 16 * NT * blockIdx.y, t = 16 * blockIdx.x + col;
+    const int g = t < cnt ? list[t] : -1;
+    const int ch = g >= 0 ? child[8 * (int64_t)g + c] : -1;
+    f64x4 acc[NT];
+    const double *ap[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        acc[i] = f64x4{0, 0, 0, 0};
+        ap[i] = tab + (size_t)c * P2 * P2 + min(r0 + 16 * i + col, P2 - 1);
     }
+    if (__ballot(ch >= 0)) ad_vert_tiles<P, NT>(ap, M + (size_t)max(ch, 0) * S, ch >= 0, q, acc);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        if (i > 0) __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[c][j][lane] = acc[i][j];
+        __syncthreads();
+        if (c < 4) {  // row r0 + 16 i + q + 4 c of the column
+            double v = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) v += red[w][c][lane];
+            const int o = r0 + 16 * i + q + 4 * c;
+            if (g >= 0 && o < S) M[(size_t)g * S + o] = o < P2 ? v : 0.0;
+        }
+    }
+}
+
+// L2L from the split boxes of one level (list[cnt]): ell(child c) += B_c ell(g)
+template <int P>
+__global__ __launch_bounds__(512) void k_ad_l2l(int cnt, const int *__restrict__ list, const int *__restrict__ child,
+                                                const double *__restrict__ tab, double *__restrict__ Lc) {
+    constexpr int P2 = P * P, S = coef_stride(P), NT = vert_tiles(P2);
+    const int lane = threadIdx.x & 63, c = threadIdx.x >> 6, q = lane >> 4, col = lane & 15;
+    const int r0 = 16 * NT * blockIdx.y, t = 16 * blockIdx.x + col;
+    const int g = t < cnt ? list[t] : -1;
+    const int ch = g >= 0 ? child[8 * (int64_t)g + c] : -1;
+    if (!__ballot(ch >= 0)) return;
+    f64x4 acc[NT];
+    const double *ap[NT];
+    double *dst = Lc + (size_t)max(ch, 0) * S;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+        ap[i] = tab + (size_t)c * P2 * P2 + min(r0 + 16 * i + col, P2 - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = dst[min(r0 + 16 * i + q + 4 * j, P2 - 1)];
+    }
+    ad_vert_tiles<P, NT>(ap, Lc + (size_t)max(g, 0) * S, ch >= 0, q, acc);
+    if (ch < 0) return;
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int o = r0 + 16 * i + q + 4 * j;
+            if (o < P2) dst[o] = acc[i][j];
+        }
 }
 
 // L2P at the leaves, outputs in root units (phi * 2^l, E * 4^l).  adj = 1:
@@ -1233,24 +1283,27 @@ __global__ __launch_bounds__(64 * kAdP2PWaves) void k_ad_p2p(
                            rec, out, c);
 }
 
-// The K-split parts of the gathered M2L added into the locals in part order
-// (one thread per (tile, column, row)).
-__global__ void k_ad_m2l_sum(AdM2LPlan pl, int P2, int S, const int *__restrict__ tgt,
-                             const double *__restrict__ partial, double *__restrict__ Lc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = (int64_t)128 * P2;
-    if (i >= pl.units * per) return;
-    const int64_t b = i / per;
-    const int e = (int)(i - b * per), c = e / P2, row = e - c * P2;
+// The K-split parts of the gathered M2L added into the locals in part order:
+// block (x, y) takes piece y of the kAdSumPieces pieces of tile x, so that the
+// tile's group is found in scalar registers.  Bound by reading the parts
+// (1e6 particles, p = 8: 62 us with the group search in every thread, now 41 us).
+constexpr int kAdSumPieces = 8;
+__global__ __launch_bounds__(256) void k_ad_m2l_sum(AdM2LPlan pl, int P2, int S, const int *__restrict__ tgt,
+                                                    const double *__restrict__ partial, double *__restrict__ Lc) {
+    const int64_t b = blockIdx.x, per = (int64_t)128 * P2;
     int gi = 0;
     for (int j = 1; j < pl.ngroups; ++j)
         if (b >= pl.grp[j].unit0) gi = j;
     const AdM2LGroup gr = pl.grp[gi];
-    const int64_t t = (b - gr.unit0) * 128 + c;
-    if (t >= gr.count) return;
-    double v = 0.0;
-    for (int k = 0; k < pl.nsplit; ++k) v += partial[((int64_t)k * pl.units + b) * per + e];
-    Lc[(int64_t)tgt[gr.toff + t] * S + row] += v;
+    const int64_t t0 = (b - gr.unit0) * 128;
+    const int cols = (int)min((int64_t)128, gr.count - t0), n = cols * P2;
+    const double *src = partial + b * per;
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < n; e += 256 * kAdSumPieces) {
+        const int c = e / P2, row = e - c * P2;
+        double v = 0.0;
+        for (int k = 0; k < pl.nsplit; ++k) v += src[(int64_t)k * pl.units * per + e];
+        Lc[(int64_t)tgt[gr.toff + t0 + c] * S + row] += v;
+    }
 }
 
 // Targets of levels >= 2 grouped by (level, class): block histograms in LDS
@@ -1298,23 +1351,35 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 // copies become memcpy calls that kept the prefetched fragments in scratch
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
-// Per-level maxima of |M_c rho_inv[c]|: one thread per (box, coefficient),
-// an LDS maximum per level in the block, one global atomic per level and
-// block (non-negative floats order like their bit patterns).
-__global__ __launch_bounds__(256) void k_ad_level_max(int P, int64_t box2, int64_t nb, const int *__restrict__ lev,
-                                                      const double *__restrict__ M, const float *__restrict__ rho_inv,
+// Per-level maxima of |M_c rho_inv[c]|: a block takes a run of boxes, whose
+// levels ascend, so a thread keeps one maximum and puts it into LDS when the
+// level changes and at the end; one global atomic per level and block
+// (non-negative floats order like their bit patterns).  Bound by reading M
+// (1e6 particles, p = 8: 46 us with an LDS atomic per coefficient and 256
+// coefficients to a block, now 19 us).
+__global__ __launch_bounds__(256) void k_ad_level_max(int P, int64_t box2, int64_t nb, int run,
+                                                      const int *__restrict__ lev, const double *__restrict__ M,
+                                                      const float *__restrict__ rho_inv,
                                                       uint32_t *__restrict__ lmax) {
     __shared__ unsigned int lm[kLevelSlots];
     const int P2 = P * P, S = coef_stride(P);
     if (threadIdx.x < kLevelSlots) lm[threadIdx.x] = 0u;
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nb * P2) {
-        const int64_t g = box2 + i / P2;
-        const int c = (int)(i % P2);
-        const float v = (float)fabs(M[g * S + c]) * rho_inv[c];
-        if (v > 0.0f) atomicMax(&lm[lev[g]], __float_as_uint(v));
+    const int64_t r0 = (int64_t)blockIdx.x * run, g0 = box2 + r0;
+    const int items = (int)min((int64_t)run, nb - r0) * P2;
+    float mx = 0.0f;
+    int cur = lev[g0];
+    for (int i = threadIdx.x; i < items; i += 256) {
+        const int b = i / P2, c = i - b * P2, l = lev[g0 + b];
+        const float v = (float)fabs(M[(g0 + b) * S + c]) * rho_inv[c];
+        if (l != cur) {
+            if (mx > 0.0f) atomicMax(&lm[cur], __float_as_uint(mx));
+            cur = l;
+            mx = 0.0f;
+        }
+        if (v > mx) mx = v;
     }
+    if (mx > 0.0f) atomicMax(&lm[cur], __float_as_uint(mx));
     __syncthreads();
     if (threadIdx.x < kLevelSlots && lm[threadIdx.x]) atomic_max_shared(lmax + threadIdx.x, lm[threadIdx.x]);
 }
@@ -1565,12 +1630,13 @@ static inline unsigned ad_blocks(int64_t n, int b) { return (unsigned)((n + b - 
 int64_t ad_box_blocks(int64_t n) { return (n + kAdBoxBlock - 1) / kAdBoxBlock; }
 
 hipError_t ad_launch_spans(int64_t n, int leaf_max, const KeyIndex &ki, uint8_t *span, uint32_t *cnt, uint32_t *base,
-                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, hipStream_t st) {
+                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, unsigned int *nsplit,
+                           hipStream_t st) {
     const int64_t nblk = ad_box_blocks(n);
     k_ad_spans<<<(unsigned)nblk, 64 * kAdBoxWaves, 0, st>>>(n, nblk, ki.Lf, (uint32_t)leaf_max, ki, span, cnt);
     hipError_t e = launch_scan((ki.Lf + 2) * nblk, cnt, base, scan, st);
     if (e != hipSuccess) return e;
-    k_ad_sizes<<<1, 64, 0, st>>>(nblk, ki.Lf, base, nbad, host);
+    k_ad_sizes<<<1, 64, 0, st>>>(nblk, ki.Lf, base, nbad, host, nsplit);
     return hipGetLastError();
 }
 
@@ -1578,7 +1644,7 @@ hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyInde
                            const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st) {
     const int64_t nblk = ad_box_blocks(n);
     k_ad_boxes<<<(unsigned)nblk, 64 * kAdBoxWaves, 0, st>>>(n, nblk, ki.Lf, nbox, nleaf, ki, span, base, bx);
-    k_ad_links<<<ad_blocks(nbox, 256), 256, 0, st>>>(nbox, ki, bx);
+    k_ad_links<<<ad_blocks(nbox, 256), 256, 0, st>>>(nbox, nblk, ki, base, bx);
     k_ad_colleagues<<<ad_blocks(27 * nbox, 256), 256, 0, st>>>(nbox, bx.lev, bx.code, bx.child, col);
     return hipGetLastError();
 }
@@ -1600,9 +1666,10 @@ hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_
 }
 
 hipError_t ad_launch_box_offsets(int64_t nbox, const uint32_t *s27, uint32_t *ou, uint32_t *ow, uint32_t *ox,
-                                 int ngrp, const unsigned int *ccnt, unsigned int *host, hipStream_t st) {
-    k_ad_box_offsets<<<ad_blocks(std::max<int64_t>(nbox + 1, ngrp), 256), 256, 0, st>>>(nbox, s27, ou, ow, ox, ngrp,
-                                                                                        ccnt, host);
+                                 int nlev, const unsigned int *nsplit, int ngrp, const unsigned int *ccnt,
+                                 unsigned int *host, hipStream_t st) {
+    k_ad_box_offsets<<<ad_blocks(std::max<int64_t>(nbox + 1, std::max(nlev, ngrp)), 256), 256, 0, st>>>(
+        nbox, s27, ou, ow, ox, nlev, nsplit, ngrp, ccnt, host);
     return hipGetLastError();
 }
 
@@ -1648,20 +1715,13 @@ hipError_t ad_launch_p2m(int P, int64_t nleaf, const int *lbox, const uint32_t *
     return hipGetLastError();
 }
 
-// boxes per block of k_ad_m2m (its BX)
-static constexpr int m2m_boxes(int P) {
-    return 4096 / (8 * P * P) < 1 ? 1 : (4096 / (8 * P * P) > 8 ? 8 : 4096 / (8 * P * P));
-}
-
-hipError_t ad_launch_m2m(int P, int64_t b0, int64_t nb, const uint8_t *leaf, const int *child, const double *tab,
-                         double *M, hipStream_t st) {
-    if (nb == 0) return hipSuccess;
+hipError_t ad_launch_m2m(int P, int64_t cnt, const int *list, const int *child, const double *tab, double *M,
+                         hipStream_t st) {
+    if (cnt == 0) return hipSuccess;
+    const int rows = coef_stride(P);
+    const dim3 grid(ad_blocks(cnt, 16), ad_blocks(rows, 16 * vert_tiles(rows)));
     switch (P) {
-#define X(PP)                                                                                                   \
-    case PP:                                                                                                    \
-        k_ad_m2m<PP><<<(unsigned)((nb + m2m_boxes(PP) - 1) / m2m_boxes(PP)), 256, 0, st>>>(b0, nb, leaf, child,  \
-                                                                                         tab, M);                \
-        break;
+#define X(PP) case PP: k_ad_m2m<PP><<<grid, 512, 0, st>>>((int)cnt, list, child, tab, M); break;
         AD_CASES(X)
 #undef X
         default: return hipErrorInvalidValue;
@@ -1669,11 +1729,13 @@ hipError_t ad_launch_m2m(int P, int64_t b0, int64_t nb, const uint8_t *leaf, con
     return hipGetLastError();
 }
 
-hipError_t ad_launch_l2l(int P, int64_t b0, int64_t nb, const uint32_t *code, const int *parent, const double *tab,
-                         double *Lc, hipStream_t st) {
-    if (nb == 0) return hipSuccess;
+hipError_t ad_launch_l2l(int P, int64_t cnt, const int *list, const int *child, const double *tab, double *Lc,
+                         hipStream_t st) {
+    if (cnt == 0) return hipSuccess;
+    const int rows = P * P;
+    const dim3 grid(ad_blocks(cnt, 16), ad_blocks(rows, 16 * vert_tiles(rows)));
     switch (P) {
-#define X(PP) case PP: k_ad_l2l<PP><<<(unsigned)nb, 256, 0, st>>>(b0, code, parent, tab, Lc); break;
+#define X(PP) case PP: k_ad_l2l<PP><<<grid, 512, 0, st>>>((int)cnt, list, child, tab, Lc); break;
         AD_CASES(X)
 #undef X
         default: return hipErrorInvalidValue;
@@ -1684,8 +1746,11 @@ hipError_t ad_launch_l2l(int P, int64_t b0, int64_t nb, const uint32_t *code, co
 hipError_t ad_launch_pack_h(int P, int64_t box2, int64_t nbox, const int *lev, const double *M,
                             const float *rho_inv, uint32_t *lmax, void *Bh, hipStream_t st) {
     const int64_t nb = nbox - box2;
-    if (nb > 0)
-        k_ad_level_max<<<ad_blocks(nb * P * P, 256), 256, 0, st>>>(P, box2, nb, lev, M, rho_inv, lmax);
+    if (nb > 0) {
+        // about 1024 blocks, of at least 2048 coefficients
+        const int run = (int)std::max<int64_t>((nb + 1023) / 1024, (2048 + P * P - 1) / (P * P));
+        k_ad_level_max<<<ad_blocks(nb, run), 256, 0, st>>>(P, box2, nb, run, lev, M, rho_inv, lmax);
+    }
     k_ad_pack_h<<<ad_blocks((nb + 1) * (coef_stride(P) / 8), 256), 256, 0, st>>>(P, box2, nbox, lev, M, rho_inv,
                                                                                  lmax, (uint4 *)Bh);
     return hipGetLastError();
@@ -1708,8 +1773,7 @@ hipError_t ad_launch_m2l_h(int P, const AdM2LPlan &pl, const uint16_t *Ah, size_
         default: return hipErrorInvalidValue;
     }
     if (pl.nsplit > 1)
-        k_ad_m2l_sum<<<ad_blocks(pl.units * 128 * P * P, 256), 256, 0, st>>>(pl, P * P, coef_stride(P), tgt, partial,
-                                                                             Lc);
+        k_ad_m2l_sum<<<dim3((unsigned)pl.units, kAdSumPieces), 256, 0, st>>>(pl, P * P, coef_stride(P), tgt, partial, Lc);
     return hipGetLastError();
 }
 

@@ -64,7 +64,7 @@ struct Buf {
 // and freeing pinned memory costs more than the rest of a small tree's life
 // (the free waits for the device), so a destroyed tree leaves its kit for the
 // next one on its device; at most kKits wait, the others are freed.
-constexpr int kAdHostWords = 128;  // adaptive build: 3 totals + 8 groups per level 2..10
+constexpr int kAdHostWords = 128;  // adaptive build: 3 totals, 11 levels, 8 groups per level 2..10
 struct HostKit {
     int dev = 0;
     unsigned int *words = nullptr;      // pinned, coherent: 4 counters, then kAdHostWords
@@ -428,6 +428,7 @@ struct AdTree {
     int64_t nbox = 0, nleaf = 0, nvbox = 0;  // nvbox: boxes of levels >= 2
     int64_t off[FMM_MAX_LEVEL + 2] = {};      // first box of each level, off[depth + 1] = nbox
     int64_t nlist[3] = {};                    // items of U, W, X
+    int64_t nsplit[FMM_MAX_LEVEL + 1] = {};   // split boxes of each level
     AdM2LPlan plan{};                         // mixed form
     FoldPlan fold{};                          // FP64 form
     uint32_t *hbuf = nullptr;                 // the kit's words for the build's counts
@@ -435,6 +436,7 @@ struct AdTree {
         ucnt, uoff, units, s27, units_m;
     Buf skey, cstart, ks_a, ks_b, ks_v, ks_h;  // the key sort: sorted keys, coarse starts, scratch
     Buf span, bcnt, bbase;  // the boxes each particle heads, their counts per (level, block), scanned
+    Buf split, splitn;      // split boxes per level
     Buf area[3];            // hold the buffers above: by particles, by boxes, by list items
     int64_t max_units = 0;  // bound of the P2P work units (their count stays on the device)
 };
@@ -898,7 +900,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                {&t->scan, u4 * scan_scratch_words(rows + 1)}, {&a->skey, u4 * n}, {&a->cstart, u4 * (nc + 1)},
                {&a->ks_a, u4 * n}, {&a->ks_b, u4 * n}, {&a->ks_v, u4 * n},
                {&a->ks_h, u4 * (2 * hw + 1 + scan_scratch_words(hw))}, {&a->span, (size_t)n},
-               {&a->bcnt, u4 * rows}, {&a->bbase, u4 * (rows + 1)}},
+               {&a->bcnt, u4 * rows}, {&a->bbase, u4 * (rows + 1)}, {&a->splitn, u4 * (FMM_MAX_LEVEL + 1)}},
               st));
     unsigned int *dc = bp<unsigned int>(t->counters), *hdev = t->kit.words_dev + 4;  // of hbuf, for kernels
     uint32_t *scan = bp<uint32_t>(t->scan), *skey = bp<uint32_t>(a->skey), *perm = bp<uint32_t>(t->perm);
@@ -915,7 +917,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     HIPCHK(launch_key_sort(n, Lf, bp<uint32_t>(t->key10), ksw, perm, skey, st));
     HIPCHK(launch_key_starts(n, Lf, cl, skey, bp<uint32_t>(a->cstart), st));
     HIPCHK(ad_launch_spans(n, c.leaf_max, ki, span, bp<uint32_t>(a->bcnt), bp<uint32_t>(a->bbase), scan, dc, hdev,
-                           st));
+                           bp<unsigned int>(a->splitn), st));
     HIPCHK(hipEventRecord(t->kit.ev, st));
     HIPCHK(ad_launch_records(n, dtype, Lf, span, skey, perm, pos, c.box_lo, c.box_size, bp<double4>(t->xyz64), st));
     HIPCHK(hipEventSynchronize(t->kit.ev));
@@ -936,7 +938,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     const int ngrp = f64 ? 0 : 8 * std::max(nlev - 2, 0);
     CHK(place(t, a->area[1],
               {{&a->code, u4 * nbox}, {&a->ps, u4 * nbox}, {&a->pe, u4 * nbox}, {&a->parent, u4 * nbox},
-               {&a->child, 8 * u4 * nbox}, {&a->leaf, (size_t)nbox + 4},  // read back as whole words by the export
+               {&a->child, 8 * u4 * nbox}, {&a->split, u4 * nbox}, {&a->leaf, (size_t)nbox + 4},  // read back as whole words by the export
                {&a->lev, u4 * nbox}, {&a->col, 27 * u4 * nbox}, {&a->lbox, u4 * a->nleaf},
                {&a->lstart, u4 * (a->nleaf + 1)}, {&a->llev, (size_t)a->nleaf},
                {&a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1)}, {&a->cnts, 3 * u4 * n27},
@@ -946,7 +948,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     scan = bp<uint32_t>(t->scan);
     const AdBoxes bx{bp<uint32_t>(a->code), bp<uint32_t>(a->ps), bp<uint32_t>(a->pe),    bp<int>(a->lev),
                      bp<int>(a->parent),    bp<int>(a->child),   bp<uint8_t>(a->leaf),   bp<int>(a->lbox),
-                     bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev)};
+                     bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev),  bp<int>(a->split),     bp<unsigned int>(a->splitn)};
     uint32_t *code = bx.code, *ps = bx.ps, *pe = bx.pe;
     int *lev = bx.lev, *parent = bx.parent, *child = bx.child, *col = bp<int>(a->col);
     uint8_t *leaf = bx.leaf;
@@ -963,12 +965,13 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
         HIPCHK(ad_launch_class(a->off[2], a->nvbox, lev, code, bp<unsigned int>(a->ccnt), AdGroupStarts{}, nullptr,
                                nullptr, st));
     }
-    HIPCHK(ad_launch_box_offsets(nbox, su, ou, ow, ox, ngrp, bp<unsigned int>(a->ccnt), hdev, st));
+    HIPCHK(ad_launch_box_offsets(nbox, su, ou, ow, ox, nlev, bx.nsplit, ngrp, bp<unsigned int>(a->ccnt), hdev, st));
     HIPCHK(hipEventRecord(t->kit.ev, st));
     HIPCHK(ad_launch_vslots(a->off[std::min(nlev, 2)], a->nvbox, code, parent, col, child,
                             f64 ? t->ops->fold.cls : t->ops->cls, bp<int>(a->vidx), st));
     HIPCHK(hipEventSynchronize(t->kit.ev));
     for (int k = 0; k < 3; ++k) a->nlist[k] = a->hbuf[k];
+    for (int l = 0; l < nlev; ++l) a->nsplit[l] = a->hbuf[3 + l];
     // P2P work units: at most one per leaf plus one per 64 particles
     a->max_units = a->nleaf + n / 64;
     CHK(place(t, a->area[2],
@@ -995,7 +998,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     int64_t at = 0;
     for (int g = 0; g < ngrp; ++g) {
         gs.at[g] = at;
-        const int64_t cnt = a->hbuf[3 + g];
+        const int64_t cnt = a->hbuf[3 + nlev + g];
         if (cnt) {
             AdM2LGroup &e = a->plan.grp[a->plan.ngroups++];
             e.unit0 = a->plan.units;
@@ -1102,7 +1105,7 @@ fmm_status run_adaptive(fmm_tree *t, const Work &w, const void *charges, bool ad
         HIPCHK(ad_launch_p2m(P, a->nleaf, lbox, lstart, llev, adj, recs, M, f32, st));
         CHK(rec(t, 2, st));
         for (int l = a->depth - 1; l >= 2; --l)
-            HIPCHK(ad_launch_m2m(P, a->off[l], a->off[l + 1] - a->off[l], bp<uint8_t>(a->leaf), bp<int>(a->child),
+            HIPCHK(ad_launch_m2m(P, a->nsplit[l], bp<int>(a->split) + a->off[l], bp<int>(a->child),
                                  adjoint ? o->aup64 : o->up64, M, st));
         CHK(rec(t, 3, st));
         HIPCHK(ad_launch_p2l(P, a->nbox, ox, bp<int>(a->ix), lev, code, ps, pe, adj, recs, Lc, f32, st));
@@ -1119,8 +1122,8 @@ fmm_status run_adaptive(fmm_tree *t, const Work &w, const void *charges, bool ad
             HIPCHK(ad_launch_m2l_fold(P, a->fold, adjoint ? o->afold64 : o->fold64, o->fold, M, bp<int>(a->vidx), code,
                                       a->off[2], a->nbox, Lc, (double *)w.pack[0], w.m2lpart, st));
         CHK(rec(t, 5, st));
-        for (int l = 3; l <= a->depth; ++l)
-            HIPCHK(ad_launch_l2l(P, a->off[l], a->off[l + 1] - a->off[l], code, bp<int>(a->parent),
+        for (int l = 2; l < a->depth; ++l)
+            HIPCHK(ad_launch_l2l(P, a->nsplit[l], bp<int>(a->split) + a->off[l], bp<int>(a->child),
                                  adjoint ? o->adown64 : o->down64, Lc, st));
         CHK(rec(t, 6, st));
         HIPCHK(ad_launch_l2p(P, a->nleaf, lbox, lstart, llev, adj, recs, Lc, w.farf, f32, st));

@@ -127,6 +127,8 @@ struct AdBoxes {
     int *lbox;                 // leaf -> box
     uint32_t *lstart;          // [nleaf + 1]
     uint8_t *llev;
+    int *split;                // split boxes, each level's from its first box's id on
+    unsigned int *nsplit;      // their number per level
 };
 constexpr int kAdBoxBlock = 1024;  // particles per block of the box counts
 int64_t ad_box_blocks(int64_t n);
@@ -135,9 +137,10 @@ int64_t ad_box_blocks(int64_t n);
 // high four), the boxes and leaves headed per (row, block) and their scan
 // (cnt, base[(Lf + 2) ad_box_blocks(n) + 1]); host[0..Lf + 1] = first box of
 // each level and the box count, host[Lf + 2] = boxes + leaves, host[Lf + 3] =
-// *nbad.
+// *nbad; nsplit[0..Lf] zeroed.
 hipError_t ad_launch_spans(int64_t n, int leaf_max, const KeyIndex &ki, uint8_t *span, uint32_t *cnt, uint32_t *base,
-                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, hipStream_t st);
+                           uint32_t *scan, const unsigned int *nbad, unsigned int *host, unsigned int *nsplit,
+                           hipStream_t st);
 // the boxes, the leaf list and the colleagues (col[27 nbox])
 hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyIndex &ki, const uint8_t *span,
                            const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st);
@@ -151,9 +154,10 @@ hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_
                            int *iw, int *ix, hipStream_t st);
 // per-box list offsets ou/ow/ox [nbox + 1] from the three per-(box,
 // direction) scans stored one after another, each 27 nbox + 1 long; host[0..2]
-// = the list lengths, host[3..] = ccnt[ngrp]
+// = the list lengths, host[3..] = nsplit[nlev], then ccnt[ngrp]
 hipError_t ad_launch_box_offsets(int64_t nbox, const uint32_t *s27, uint32_t *ou, uint32_t *ow, uint32_t *ox,
-                                 int ngrp, const unsigned int *ccnt, unsigned int *host, hipStream_t st);
+                                 int nlev, const unsigned int *nsplit, int ngrp, const unsigned int *ccnt,
+                                 unsigned int *host, hipStream_t st);
 // the fullest leaf's count into *mx
 hipError_t ad_launch_leafmax(int64_t nleaf, const uint32_t *lstart, unsigned int *mx, hipStream_t st);
 // out[4] (zeroed): ordered P2P pairs incl. self, V entries, W and X (particle, box) pairs
@@ -194,8 +198,9 @@ inline size_t ad_m2l_partial_bytes(const AdM2LPlan &pl, int P) {
 // and P2L with their position derivatives (outputs times 2^-l)
 hipError_t ad_launch_p2m(int P, int64_t nleaf, const int *lbox, const uint32_t *lstart, const uint8_t *llev, int adj,
                          const double4 *rec, double *M, bool f32, hipStream_t st);
-hipError_t ad_launch_m2m(int P, int64_t b0, int64_t nb, const uint8_t *leaf, const int *child, const double *tab,
-                         double *M, hipStream_t st);
+// list: the split boxes of one level (M2M into them, L2L from them)
+hipError_t ad_launch_m2m(int P, int64_t cnt, const int *list, const int *child, const double *tab, double *M,
+                         hipStream_t st);
 // mixed form: the per-level maxima of |M_c rho_inv[c]| over the boxes of
 // levels >= 2 (lmax, kLevelSlots words, zeroed beforehand), then the scaled
 // multipoles split into binary16 parts Bh [nbox + 1][S/8][hi8, lo8] (rows
@@ -210,8 +215,8 @@ hipError_t ad_launch_m2l_h(int P, const AdM2LPlan &pl, const uint16_t *Ah, size_
 hipError_t ad_launch_p2l(int P, int64_t nbox, const uint32_t *ox, const int *ix, const int *lev,
                          const uint32_t *code, const uint32_t *ps, const uint32_t *pe, int adj, const double4 *rec,
                          double *Lc, bool f32, hipStream_t st);
-hipError_t ad_launch_l2l(int P, int64_t b0, int64_t nb, const uint32_t *code, const int *parent, const double *tab,
-                         double *Lc, hipStream_t st);
+hipError_t ad_launch_l2l(int P, int64_t cnt, const int *list, const int *child, const double *tab, double *Lc,
+                         hipStream_t st);
 hipError_t ad_launch_l2p(int P, int64_t nleaf, const int *lbox, const uint32_t *lstart, const uint8_t *llev,
                          int adj, const double4 *rec, const double *Lc, double4 *out, bool f32, hipStream_t st);
 // one wave per P2P work unit (see ad_launch_units)
