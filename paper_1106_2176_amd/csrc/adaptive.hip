@@ -875,14 +875,25 @@ __device__ __forceinline__ void irregular_each(R x, R y, R z, F &&f) {
 // rows summed coefficient by coefficient.  R is the arithmetic of the
 // expansion (FP32 in the mixed form, the offset formed in FP64 and rounded
 // once); the rows are summed in FP64.
+//
+// Bound by the expansions' instructions and their latency, the same for B
+// lanes as for 64.  So B is 64 where the rows leave room for two waves per
+// SIMD, else 32 or less within a quarter of the LDS.  FP64, 3e5 particles:
+// p = 12 with 32 rows (37 KB) 721 us, with 8 (9 KB) 1170; p = 10 with 32
+// 390, with 16 479; 1e6 particles, p = 8: 64 rows (33 KB) 537, 32 491.
+template <int LEN, typename R>
+constexpr int p2l_rows() {
+    int b = 64;
+    while (b > 8 && b * LEN * (int)sizeof(R) > (b == 64 ? 20 : 38) * 1024) b /= 2;
+    return b;
+}
 template <int P, typename R>
 __global__ __launch_bounds__(64) void k_ad_p2l(const uint32_t *__restrict__ ox, const int *__restrict__ ix,
                                                const int *__restrict__ lev, const uint32_t *__restrict__ code,
                                                const uint32_t *__restrict__ ps, const uint32_t *__restrict__ pe,
                                                int adj, const double4 *__restrict__ rec, double *__restrict__ Lc) {
     constexpr int P2 = P * P, S = coef_stride(P), NC = (P2 + 63) / 64;
-    // rows of at most ~17 KB (2 waves per SIMD)
-    constexpr int B = (P <= 8 ? 32 : (P <= 11 ? 16 : 8)) * (int)(sizeof(double) / sizeof(R));
+    constexpr int B = p2l_rows<P2 + 1, R>();
     __shared__ R rows[B][P2 + 1];
     __shared__ double4 frame[64];
     __shared__ uint32_t first[64], off[65];
