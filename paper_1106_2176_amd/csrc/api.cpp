@@ -436,7 +436,7 @@ struct AdTree {
         ucnt, uoff, units, s27, units_m;
     Buf skey, cstart, ks_a, ks_b, ks_v, ks_h;  // the key sort: sorted keys, coarse starts, scratch
     Buf span, bcnt, bbase;  // the boxes each particle heads, their counts per (level, block), scanned
-    Buf split, splitn;      // split boxes per level
+    Buf node, split, splitn;  // children by octants; split boxes per level
     Buf area[3];            // hold the buffers above: by particles, by boxes, by list items
     int64_t max_units = 0;  // bound of the P2P work units (their count stays on the device)
 };
@@ -938,7 +938,8 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     const int ngrp = f64 ? 0 : 8 * std::max(nlev - 2, 0);
     CHK(place(t, a->area[1],
               {{&a->code, u4 * nbox}, {&a->ps, u4 * nbox}, {&a->pe, u4 * nbox}, {&a->parent, u4 * nbox},
-               {&a->child, 8 * u4 * nbox}, {&a->split, u4 * nbox}, {&a->leaf, (size_t)nbox + 4},  // read back as whole words by the export
+               {&a->child, 8 * u4 * nbox}, {&a->node, sizeof(int2) * nbox}, {&a->split, u4 * nbox},
+               {&a->leaf, (size_t)nbox + 4},  // read back as whole words by the export
                {&a->lev, u4 * nbox}, {&a->col, 27 * u4 * nbox}, {&a->lbox, u4 * a->nleaf},
                {&a->lstart, u4 * (a->nleaf + 1)}, {&a->llev, (size_t)a->nleaf},
                {&a->vidx, (size_t)kOffsetsPerClass * u4 * std::max<int64_t>(a->nvbox, 1)}, {&a->cnts, 3 * u4 * n27},
@@ -946,19 +947,19 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                {&t->scan, u4 * scan_scratch_words(3 * n27 + 1)}, {&a->ccnt, u4 * std::max(ngrp, 1)}},
               st));
     scan = bp<uint32_t>(t->scan);
-    const AdBoxes bx{bp<uint32_t>(a->code), bp<uint32_t>(a->ps), bp<uint32_t>(a->pe),    bp<int>(a->lev),
-                     bp<int>(a->parent),    bp<int>(a->child),   bp<uint8_t>(a->leaf),   bp<int>(a->lbox),
-                     bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev),  bp<int>(a->split),     bp<unsigned int>(a->splitn)};
+    const AdBoxes bx{bp<uint32_t>(a->code),   bp<uint32_t>(a->ps),  bp<uint32_t>(a->pe), bp<int>(a->lev),
+                     bp<int>(a->parent),      bp<int>(a->child),    bp<int2>(a->node),   bp<uint8_t>(a->leaf),
+                     bp<int>(a->lbox),        bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev), bp<int>(a->split),
+                     bp<unsigned int>(a->splitn)};
     uint32_t *code = bx.code, *ps = bx.ps, *pe = bx.pe;
     int *lev = bx.lev, *parent = bx.parent, *child = bx.child, *col = bp<int>(a->col);
-    uint8_t *leaf = bx.leaf;
     uint32_t *nu = bp<uint32_t>(a->cnts), *nw = nu + n27, *nx = nw + n27;
     // the U, W and X counts (contiguous) in one scan: run k starts at k n27
     uint32_t *su = bp<uint32_t>(a->s27), *sw = su + n27, *sx = sw + n27;
     uint32_t *ou = bp<uint32_t>(a->offs), *ow = ou + nbox + 1, *ox = ow + nbox + 1;
     HIPCHK(ad_launch_boxes(n, nbox, a->nleaf, ki, span, bp<uint32_t>(a->bbase), bx, col, st));
-    HIPCHK(ad_launch_lists(nbox, 0, lev, code, parent, col, child, leaf, nu, nw, nx, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, nullptr, st));
+    HIPCHK(ad_launch_lists(nbox, false, bx, col, nu, nw, nx, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                           st));
     HIPCHK(launch_scan(3 * n27, nu, su, scan, st));
     if (ngrp) {
         HIPCHK(launch_zero(bp<uint32_t>(a->ccnt), ngrp, st));
@@ -980,8 +981,8 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                {&a->units, sizeof(int2) * a->max_units}, {&a->units_m, sizeof(int2) * a->max_units},
                {&a->tgt, ngrp ? u4 * a->nvbox : 0}},
               st));
-    HIPCHK(ad_launch_lists(nbox, 1, lev, code, parent, col, child, leaf, nu, nw, nx, su, sw, sx, bp<int>(a->iu),
-                           bp<int>(a->iw), bp<int>(a->ix), st));
+    HIPCHK(ad_launch_lists(nbox, true, bx, col, nu, nw, nx, su, sw, sx, bp<int>(a->iu), bp<int>(a->iw),
+                           bp<int>(a->ix), st));
     HIPCHK(launch_zero(dc + 3, 1, st));
     HIPCHK(ad_launch_leafmax(a->nleaf, bx.lstart, dc + 3, st));
     // work units, heaviest first: one run of nleaf counts per weight class

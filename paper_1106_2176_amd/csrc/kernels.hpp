@@ -123,6 +123,7 @@ struct KeyIndex {
 struct AdBoxes {
     uint32_t *code, *ps, *pe;  // Morton code at the box's level; its particles [ps, pe)
     int *lev, *parent, *child; // child[8 g + octant], -1: absent
+    int2 *node;                // first child; octants present | octants of leaves << 8
     uint8_t *leaf;
     int *lbox;                 // leaf -> box
     uint32_t *lstart;          // [nleaf + 1]
@@ -146,10 +147,9 @@ hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyInde
                            const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st);
 hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const uint32_t *code, const int *parent, const int *col,
                             const int *child, const int2 *cls, int *vidx, hipStream_t st);
-// one thread per (box, direction): pass 0 counts [27 nbox] each, pass 1
-// fills at the scanned per-(box, direction) offsets
-hipError_t ad_launch_lists(int64_t nbox, int pass, const int *lev, const uint32_t *code, const int *parent,
-                           const int *col, const int *child, const uint8_t *leaf, uint32_t *nu, uint32_t *nw,
+// one thread per (box, direction): the counts [27 nbox] each, or with fill
+// the items at the scanned per-(box, direction) offsets
+hipError_t ad_launch_lists(int64_t nbox, bool fill, const AdBoxes &bx, const int *col, uint32_t *nu, uint32_t *nw,
                            uint32_t *nx, const uint32_t *ou, const uint32_t *ow, const uint32_t *ox, int *iu,
                            int *iw, int *ix, hipStream_t st);
 // per-box list offsets ou/ow/ox [nbox + 1] from the three per-(box,
