@@ -303,28 +303,34 @@ __global__ __launch_bounds__(256) void k_ad_colleagues(int64_t nbox, const int *
 
 // V as slots: for box g of level >= 2 (g >= box2) and class k (its coordinate
 // parities), slot s of the class's 189 offsets holds the source box t + d if
-// it exists (a child of one of the parent's colleagues), else -1; one thread
-// per (box, slot).
+// it exists (a child of one of the parent's colleagues), else -1.  A wave per
+// box: lane c < 27 holds the parent's colleague c as its node, and a lane
+// takes slots lane, lane + 64, ..., so that a slot costs one table load and
+// two lane permutations (with a thread per slot and a load each for the
+// parent, its colleague and the child: 44 us at 60,000 boxes, now 21).
+// Outside the root cube there are no colleagues.
 __global__ __launch_bounds__(256) void k_ad_vslots(int64_t box2, int64_t nb, const uint32_t *__restrict__ code,
                                                    const int *__restrict__ parent, const int *__restrict__ col,
-                                                   const int *__restrict__ child, const int2 *__restrict__ cls,
+                                                   const int2 *__restrict__ node, const int2 *__restrict__ cls,
                                                    int *__restrict__ vidx) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)kOffsetsPerClass * nb) return;
-    const int64_t bi = i / kOffsetsPerClass;
-    const int s = (int)(i - bi * kOffsetsPerClass);
+    const int lane = threadIdx.x & 63;
+    const int64_t bi = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (bi >= nb) return;
     const int64_t g = box2 + bi;
-    const AdBox t = ad_box(0, code[g]);
-    const int k = (t.x & 1) | ((t.y & 1) << 1) | ((t.z & 1) << 2);
-    const int e = cls[k * kOffsetsPerClass + s].x;
-    const int sx = t.x + (e & 15) - 4, sy = t.y + ((e >> 4) & 15) - 4, sz = t.z + ((e >> 8) & 15) - 4;
-    int r = -1;
-    if (sx >= 0 && sy >= 0 && sz >= 0) {
-        const int ox = (sx >> 1) - (t.x >> 1), oy = (sy >> 1) - (t.y >> 1), oz = (sz >> 1) - (t.z >> 1);
-        const int pc = col[27 * (int64_t)parent[g] + (ox + 1) + 3 * (oy + 1) + 9 * (oz + 1)];
-        if (pc >= 0) r = child[8 * (int64_t)pc + ((sx & 1) | ((sy & 1) << 1) | ((sz & 1) << 2))];
+    const int pc = lane < 27 ? col[27 * (int64_t)parent[g] + lane] : -1;
+    const int2 nd = pc >= 0 ? node[pc] : make_int2(0, 0);
+    const uint32_t oct = code[g] & 7u;
+    const int px = (int)(oct & 1), py = (int)((oct >> 1) & 1), pz = (int)(oct >> 2);
+    for (int s0 = 0; s0 < kOffsetsPerClass; s0 += 64) {
+        const int s = s0 + lane;
+        const int e = cls[oct * kOffsetsPerClass + min(s, kOffsetsPerClass - 1)].x;
+        // the source relative to the parent, in units of the box: -2 .. 3
+        const int x = px + (e & 15) - 4, y = py + ((e >> 4) & 15) - 4, z = pz + ((e >> 8) & 15) - 4;
+        const int o = (x >> 1) + 1 + 3 * ((y >> 1) + 1) + 9 * ((z >> 1) + 1);
+        const int first = __shfl(nd.x, o), has = __shfl(nd.y, o) & 255;
+        const int bit = 1 << ((x & 1) | (y & 1) << 1 | (z & 1) << 2);
+        if (s < kOffsetsPerClass) vidx[kOffsetsPerClass * bi + s] = has & bit ? first + __popc(has & (bit - 1)) : -1;
     }
-    vidx[i] = r;
 }
 
 // The parts of U and W (leaf g only) and of X (any box g) that come
@@ -1675,10 +1681,10 @@ hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyInde
     return hipGetLastError();
 }
 
-hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const uint32_t *code, const int *parent, const int *col,
-                            const int *child, const int2 *cls, int *vidx, hipStream_t st) {
+hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const AdBoxes &bx, const int *col, const int2 *cls, int *vidx,
+                            hipStream_t st) {
     if (nb == 0) return hipSuccess;
-    k_ad_vslots<<<ad_blocks(kOffsetsPerClass * nb, 256), 256, 0, st>>>(box2, nb, code, parent, col, child, cls, vidx);
+    k_ad_vslots<<<ad_blocks(nb, 4), 256, 0, st>>>(box2, nb, bx.code, bx.parent, col, bx.node, cls, vidx);
     return hipGetLastError();
 }
 

@@ -952,7 +952,7 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                      bp<int>(a->lbox),        bp<uint32_t>(a->lstart), bp<uint8_t>(a->llev), bp<int>(a->split),
                      bp<unsigned int>(a->splitn)};
     uint32_t *code = bx.code, *ps = bx.ps, *pe = bx.pe;
-    int *lev = bx.lev, *parent = bx.parent, *child = bx.child, *col = bp<int>(a->col);
+    int *lev = bx.lev, *col = bp<int>(a->col);
     uint32_t *nu = bp<uint32_t>(a->cnts), *nw = nu + n27, *nx = nw + n27;
     // the U, W and X counts (contiguous) in one scan: run k starts at k n27
     uint32_t *su = bp<uint32_t>(a->s27), *sw = su + n27, *sx = sw + n27;
@@ -968,8 +968,8 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
     }
     HIPCHK(ad_launch_box_offsets(nbox, su, ou, ow, ox, nlev, bx.nsplit, ngrp, bp<unsigned int>(a->ccnt), hdev, st));
     HIPCHK(hipEventRecord(t->kit.ev, st));
-    HIPCHK(ad_launch_vslots(a->off[std::min(nlev, 2)], a->nvbox, code, parent, col, child,
-                            f64 ? t->ops->fold.cls : t->ops->cls, bp<int>(a->vidx), st));
+    HIPCHK(ad_launch_vslots(a->off[std::min(nlev, 2)], a->nvbox, bx, col, f64 ? t->ops->fold.cls : t->ops->cls,
+                            bp<int>(a->vidx), st));
     HIPCHK(hipEventSynchronize(t->kit.ev));
     for (int k = 0; k < 3; ++k) a->nlist[k] = a->hbuf[k];
     for (int l = 0; l < nlev; ++l) a->nsplit[l] = a->hbuf[3 + l];

@@ -145,8 +145,8 @@ hipError_t ad_launch_spans(int64_t n, int leaf_max, const KeyIndex &ki, uint8_t 
 // the boxes, the leaf list and the colleagues (col[27 nbox])
 hipError_t ad_launch_boxes(int64_t n, int64_t nbox, int64_t nleaf, const KeyIndex &ki, const uint8_t *span,
                            const uint32_t *base, const AdBoxes &bx, int *col, hipStream_t st);
-hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const uint32_t *code, const int *parent, const int *col,
-                            const int *child, const int2 *cls, int *vidx, hipStream_t st);
+hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const AdBoxes &bx, const int *col, const int2 *cls, int *vidx,
+                            hipStream_t st);
 // one thread per (box, direction): the counts [27 nbox] each, or with fill
 // the items at the scanned per-(box, direction) offsets
 hipError_t ad_launch_lists(int64_t nbox, bool fill, const AdBoxes &bx, const int *col, uint32_t *nu, uint32_t *nw,

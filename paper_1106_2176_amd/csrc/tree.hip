@@ -191,6 +191,27 @@ __global__ void k_scan_add(int64_t nb, int64_t nblocks, uint32_t *__restrict__ o
     out[i] += sums[i / 4096];
 }
 
+// The same from the block sums as they are, at most kScanSums of them: every
+// block adds up the sums before its own, which costs less than a launch that
+// scans them (5 us of a scan's 15 at 63,000 counts).
+constexpr int64_t kScanSums = 1024;
+__global__ __launch_bounds__(1024) void k_scan_sum_add(int64_t nb, int64_t nblocks, uint32_t *__restrict__ out,
+                                                       const uint32_t *__restrict__ sums) {
+    __shared__ uint32_t ws[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t x = threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0u;
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+    if (lane == 0) ws[wave] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int w = 0; w < 16; ++w) before += ws[w];
+    for (int k = 0; k < 4; ++k) {
+        const int64_t i = (int64_t)blockIdx.x * 4096 + 1024 * k + threadIdx.x;
+        if (i < nb) out[i] += before;
+    }
+    if (blockIdx.x == nblocks - 1 && threadIdx.x == 0) out[nb] = before + sums[nblocks - 1];
+}
+
 // Counting sort placement: leaf start + rank within the leaf (no atomics).
 __global__ void k_place(int64_t n, const uint32_t *__restrict__ key10, int shift,
                         const uint32_t *__restrict__ rank, const uint32_t *__restrict__ start,
@@ -283,29 +304,33 @@ __global__ __launch_bounds__(256) void k_fixup(int L, uint32_t skip, const uint3
 // level is too deep for a bin per key (8^L bins): the first pass takes the
 // input order as the values, so ties keep input order and the last pass's
 // values are the permutation (sorted position -> input index); the last
-// pass also writes the sorted keys.  A block takes 4096 elements, element
-// j * 256 + t of its range in thread t's step j (so the steps in order visit
-// the block's elements in index order).  Per pass one kernel writes each
+// pass also writes the sorted keys.  A block takes 256 elements a step,
+// element j * 256 + t of its range in thread t's step j (so the steps in order
+// visit the block's elements in index order), and 4 to 16 steps: as many as
+// leave 1024 blocks, since a step is a chain of barriers (n = 1e6: 21 us a
+// pass for the placement with 16 steps and 245 blocks, 9 to 20 with 4), and 16
+// from 4e6 elements on, where the histograms' scan is what grows.  Per pass one kernel writes each
 // block's digit histogram, digit-major (a scan then gives every (digit,
 // block) its output offset), and one places each element at its offset plus
 // its rank among the block's earlier elements of the same digit: within a
 // wave from ballots on the digit's bits, across waves and steps from LDS
 // counts.
-constexpr int kKsSteps = 16, kKsBlock = 256 * kKsSteps;
+static int ks_steps(int64_t n) { return (int)std::min<int64_t>(16, std::max<int64_t>(4, n / (256 * 1024))); }
+static int64_t ks_blocks(int64_t n) { return (n + 256 * ks_steps(n) - 1) / (256 * ks_steps(n)); }
 
 __device__ __forceinline__ uint32_t ks_key(bool first, int64_t e, const uint32_t *__restrict__ key10, int shift,
                                            const uint32_t *__restrict__ kin) {
     return first ? key10[e] >> shift : kin[e];
 }
 
-__global__ __launch_bounds__(256) void k_ks_hist(int64_t n, int64_t nblocks, int first,
+__global__ __launch_bounds__(256) void k_ks_hist(int64_t n, int64_t nblocks, int steps, int first,
                                                  const uint32_t *__restrict__ key10, int shift,
                                                  const uint32_t *__restrict__ kin, int bit, uint32_t *__restrict__ hist) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kKsBlock;
-    for (int j = 0; j < kKsSteps; ++j) {
+    const int64_t base = (int64_t)blockIdx.x * 256 * steps;
+    for (int j = 0; j < steps; ++j) {
         const int64_t e = base + j * 256 + threadIdx.x;
         if (e < n) atomicAdd(&h[(ks_key(first, e, key10, shift, kin) >> bit) & 255u], 1u);
     }
@@ -313,7 +338,7 @@ __global__ __launch_bounds__(256) void k_ks_hist(int64_t n, int64_t nblocks, int
     hist[(int64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-__global__ __launch_bounds__(256) void k_ks_scatter(int64_t n, int64_t nblocks, int first,
+__global__ __launch_bounds__(256) void k_ks_scatter(int64_t n, int64_t nblocks, int steps, int first,
                                                     const uint32_t *__restrict__ key10, int shift,
                                                     const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                                                     int bit, const uint32_t *__restrict__ off,
@@ -325,8 +350,8 @@ __global__ __launch_bounds__(256) void k_ks_scatter(int64_t n, int64_t nblocks, 
     goff[tid] = off[(int64_t)tid * nblocks + blockIdx.x];
     run[tid] = 0;
     const uint64_t below = (1ull << lane) - 1ull;
-    const int64_t base = (int64_t)blockIdx.x * kKsBlock;
-    for (int j = 0; j < kKsSteps; ++j) {
+    const int64_t base = (int64_t)blockIdx.x * 256 * steps;
+    for (int j = 0; j < steps; ++j) {
         const int64_t e = base + j * 256 + tid;
         const bool valid = e < n;
         const uint32_t key = valid ? ks_key(first, e, key10, shift, kin) : 0u;
@@ -463,6 +488,10 @@ hipError_t launch_scan(int64_t nb, const uint32_t *in, uint32_t *out, uint32_t *
     uint32_t *sums = scratch;
     uint32_t *sums_scan = scratch + nblocks;
     k_scan_blocks<<<(unsigned)nblocks, 1024, 0, st>>>(nb, in, out, sums);
+    if (nblocks <= kScanSums) {
+        k_scan_sum_add<<<(unsigned)nblocks, 1024, 0, st>>>(nb, nblocks, out, sums);
+        return hipGetLastError();
+    }
     hipError_t e = launch_scan(nblocks, sums, sums_scan, sums_scan + nblocks + 1, st);
     if (e != hipSuccess) return e;
     k_scan_add<<<nblk(nb, 256), 256, 0, st>>>(nb, nblocks, out, sums_scan);
@@ -512,12 +541,13 @@ hipError_t launch_pair_count(int level, const uint32_t *start, unsigned long lon
     return hipGetLastError();
 }
 
-int64_t key_sort_hist_words(int64_t n) { return 256 * ((n + kKsBlock - 1) / kKsBlock); }
+int64_t key_sort_hist_words(int64_t n) { return 256 * ks_blocks(n); }
 
 hipError_t launch_key_sort(int64_t n, int level, const uint32_t *key10, const KeySortWork &w, uint32_t *perm,
                            uint32_t *skey, hipStream_t st) {
     const int passes = (3 * level + 7) / 8, shift = 3 * (10 - level);
-    const int64_t nblocks = (n + kKsBlock - 1) / kKsBlock;
+    const int64_t nblocks = ks_blocks(n);
+    const int steps = ks_steps(n);
     if (passes == 0) {
         k_iota<<<nblk(n, 256), 256, 0, st>>>(n, perm, skey);
         return hipGetLastError();
@@ -529,10 +559,10 @@ hipError_t launch_key_sort(int64_t n, int level, const uint32_t *key10, const Ke
         const int back = passes - 1 - p;  // passes after this one
         uint32_t *kout = back == 0 ? skey : ((p & 1) ? w.keys_b : w.keys_a);
         uint32_t *vout = (back & 1) ? w.vals : perm;
-        k_ks_hist<<<(unsigned)nblocks, 256, 0, st>>>(n, nblocks, p == 0, key10, shift, kin, 8 * p, w.hist);
+        k_ks_hist<<<(unsigned)nblocks, 256, 0, st>>>(n, nblocks, steps, p == 0, key10, shift, kin, 8 * p, w.hist);
         hipError_t e = launch_scan(256 * nblocks, w.hist, w.off, w.scan, st);
         if (e != hipSuccess) return e;
-        k_ks_scatter<<<(unsigned)nblocks, 256, 0, st>>>(n, nblocks, p == 0, key10, shift, kin, vin, 8 * p, w.off,
+        k_ks_scatter<<<(unsigned)nblocks, 256, 0, st>>>(n, nblocks, steps, p == 0, key10, shift, kin, vin, 8 * p, w.off,
                                                         kout, vout);
         kin = kout;
         vin = vout;
