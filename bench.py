@@ -228,7 +228,7 @@ def rooflines(wl, res, precision, enc, on_profiled):
     if not f64:
         p2p["peak_unpacked"] = PEAK_FP32_UNPACKED_TFLOPS
         p2p["frac_unpacked"] = p2p_tf / PEAK_FP32_UNPACKED_TFLOPS
-    if f64:
+    if f64:  # the dense products' FLOP; the folded kernel (k_m2l_fold) does 56/189 of them
         m2l = {"kernel": "k_m2l_f64<%d>" % wl.p, "bound": "mfma", "achieved": m2l_tf,
                "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": m2l_tf / PEAK_FP64_TFLOPS,
                "traffic": None}
@@ -261,14 +261,14 @@ def sampled_errors(res, q_np, t_idx, phi_d, E_d):
 
 
 def adaptive_rooflines(p, res):
-    """(dominant, other) rooflines of the adaptive tree's M2L (gathered FP64
+    """(dominant, other) rooflines of the adaptive tree's M2L (folded FP64
     MFMA, 2 p^4 FLOP per V entry) and P2P (FP64, 19 FLOP per pair)."""
     info, st = res["info"], res["stages_ms"]
     m2l_ms = res["dom_ms"] if res["dom"] == "M2L" else st["M2L"]
     p2p_ms = res["dom_ms"] if res["dom"] == "P2P" else st["P2P"]
     m2l_tf = 2.0 * p ** 4 * info["m2l_pairs"] / (m2l_ms * 1e-3) / 1e12
     p2p_tf = P2P_FLOP_PER_PAIR * info["p2p_pairs"] / (p2p_ms * 1e-3) / 1e12
-    m2l = {"kernel": "k_ad_m2l<%d>" % p, "bound": "mfma", "achieved": m2l_tf, "peak": PEAK_FP64_TFLOPS,
+    m2l = {"kernel": "k_ad_m2l_fold<%d>" % p, "bound": "mfma", "achieved": m2l_tf, "peak": PEAK_FP64_TFLOPS,
            "unit": "TFLOP/s", "frac": m2l_tf / PEAK_FP64_TFLOPS, "traffic": None, "ms": m2l_ms,
            "flop_per_launch": 2.0 * p ** 4 * info["m2l_pairs"]}
     p2p = {"kernel": "k_ad_p2p", "bound": "alu", "achieved": p2p_tf, "peak": PEAK_FP64_TFLOPS,

@@ -97,7 +97,7 @@ __device__ __forceinline__ uint32_t key_start(const KeyIndex &ki, uint64_t x) {
 // Both kernels are bound by the latency of their loads (n = 1e6, 32 particles
 // per leaf on average, levels to 10: 36 and 16 us).  They stand for a count,
 // a scan, a fill and a host read of the child count per level, eleven times:
-// the whole build took 1.23 ms with those and takes 0.64 ms.
+// a step (build and evaluation) took 3.45 ms with those, 2.90 without.
 constexpr int kAdBoxWaves = 4;  // waves per block, each on 256 consecutive particles
 static_assert(kAdBoxBlock == 256 * kAdBoxWaves, "four chunks of 64 particles per wave");
 
