@@ -230,9 +230,10 @@ typedef struct {
  * coordinate equal to lo + size is clamped into the last box), FMM_ENOMEM
  * (the allocator callback returned NULL, or hipMallocAsync failed),
  * FMM_EDEVICE.  On error a newly created tree is destroyed and *out is set
- * to NULL; a tree passed in for reuse stays valid for fmm_tree_destroy only
- * (except after the FMM_EINVAL of a settings mismatch, which leaves it
- * untouched).
+ * to NULL; a tree passed in for reuse stays valid for fmm_tree_destroy and
+ * another rebuild only (every other call on it returns FMM_EDEVICE until a
+ * rebuild succeeds), except after the FMM_EINVAL of a settings mismatch, which
+ * leaves it untouched.
  */
 fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const void *pos,
                           void *stream, fmm_tree **out);

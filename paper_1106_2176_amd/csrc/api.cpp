@@ -57,7 +57,6 @@ void ensure_pool(int dev) {
 struct Buf {
     void *p = nullptr;
     size_t cap = 0;
-    bool part = false;  // lies in another buffer (place())
 };
 
 // Pinned words for a build's counts and the event behind them.  Allocating
@@ -460,6 +459,7 @@ struct fmm_tree {
     Buf pairs;
     HostKit kit;
     bool kit_idle = false;      // the last build has read its counts
+    bool built = false;         // the last build succeeded
     bool strayed = false;       // used on a stream other than its build's
     Ops *ops = nullptr;
     hipEvent_t ev[kTimeRing][kEvents] = {};
@@ -588,23 +588,33 @@ void release(fmm_tree *t, Buf &b, hipStream_t st) {
 
 // Lay buffers of the given sizes one after another, 256-byte aligned, in
 // `area` (grown through the tree's allocator where it is too small; what it
-// held is then lost).  One allocation in the place of many: each call of the
-// caller's allocator costs microseconds.
+// held is then lost, and the buffers are empty where it cannot grow).  One
+// allocation in the place of many: each call of the caller's allocator costs
+// microseconds.
 struct Want {
     Buf *b;
     size_t bytes;
 };
 fmm_status place(fmm_tree *t, Buf &area, std::initializer_list<Want> want, hipStream_t st) {
     size_t total = 0;
-    for (const Want &w : want) total += (std::max<size_t>(w.bytes, 1) + 255) & ~(size_t)255;
+    for (const Want &w : want) {
+        *w.b = Buf{};
+        total += (std::max<size_t>(w.bytes, 1) + 255) & ~(size_t)255;
+    }
     const fmm_status s = ensure(t, area, total, st);
     if (s != FMM_OK) return s;
     size_t off = 0;
     for (const Want &w : want) {
-        *w.b = Buf{(unsigned char *)area.p + off, w.bytes, true};
+        *w.b = Buf{(unsigned char *)area.p + off, w.bytes};
         off += (std::max<size_t>(w.bytes, 1) + 255) & ~(size_t)255;
     }
     return FMM_OK;
+}
+
+// A rebuild that failed leaves buffers of two builds, some of them given back:
+// nothing may read them, by a captured graph or otherwise, until one succeeds.
+fmm_status check_built(const fmm_tree *t) {
+    return t->built ? FMM_OK : fail(FMM_EDEVICE, "the tree's last rebuild failed");
 }
 
 fmm_status validate_cfg(const fmm_config *c) {
@@ -1330,6 +1340,7 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
         }
         return s;
     };
+    t->built = t->kit_idle = false;
     t->cfg = *cfg;
     t->dtype = dtype;
     t->n = n;
@@ -1345,7 +1356,6 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
     if (!t->al.fa) ensure_pool(t->dev);
     if (!t->kit.words && kit_get(t->dev, t->kit) != hipSuccess)
         return bail(fail(FMM_EDEVICE, "cannot allocate pinned host memory"));
-    t->kit_idle = false;
     fmm_status s;
     // S1: smallest level whose fullest leaf holds <= leaf_max; the coarsest
     // candidate is the first level with 8^l * leaf_max >= n (fewer boxes
@@ -1358,7 +1368,7 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
     while (lev < cfg->max_level && ((int64_t)1 << (3 * lev)) * (int64_t)cfg->leaf_max < n) ++lev;
     if (cfg->adaptive) {
         if ((s = build_adaptive(t, n, dtype, pos, st)) != FMM_OK) return bail(s);
-        t->kit_idle = true;
+        t->built = t->kit_idle = true;
         *out = t;
         return FMM_OK;
     }
@@ -1432,6 +1442,7 @@ fmm_status fmm_build_tree(const fmm_config *cfg, int64_t n, int32_t dtype, const
     if (lev >= 2 && cfg->precision == FMM_PREC_FP64 && cfg->m2l_rotation && !t->ops->rot64 &&
         (s = build_rot_ops(cfg->p, t->ops)) != FMM_OK)
         return bail(s);
+    t->built = true;
     *out = t;
     return FMM_OK;
 }
@@ -1443,6 +1454,7 @@ fmm_status fmm_evaluate(fmm_tree *t, const void *q, void *phi, void *vec, int32_
     if (kind == 3 || (part != 0 && part != FMM_PART_NEAR_ONLY && part != FMM_PART_FAR_ONLY))
         return fail(FMM_EINVAL, "unknown flags");
     if (kind != FMM_VEC_NONE && !vec) return fail(FMM_EINVAL, "vec is NULL");
+    CHK(check_built(t));
     hipStream_t st = (hipStream_t)stream;
     if (st != t->stream) t->strayed = true;
     if (!t->cfg.graph) return evaluate_chain(t, q, phi, vec, flags, st);
@@ -1461,6 +1473,7 @@ fmm_status fmm_evaluate_noalloc(fmm_tree *t, const void *q, void *phi, void *vec
     if (kind == 3 || (part != 0 && part != FMM_PART_NEAR_ONLY && part != FMM_PART_FAR_ONLY))
         return fail(FMM_EINVAL, "unknown flags");
     if (kind != FMM_VEC_NONE && !vec) return fail(FMM_EINVAL, "vec is NULL");
+    CHK(check_built(t));
     if (t->L >= 2 && !t->ops) return fail(FMM_EINVAL, "the tree has no translation tables");
     // serial order, no events, no graph: nothing here creates a stream, an
     // event or a buffer
@@ -1476,6 +1489,7 @@ fmm_status fmm_backward(fmm_tree *t, const void *q, const void *w, const void *f
     if (!t || !q || !w) return fail(FMM_EINVAL, "tree, q and w are required");
     if (grad_pos && !field_fwd) return fail(FMM_EINVAL, "field_fwd is required for grad_pos");
     if (!grad_q && !grad_pos) return FMM_OK;
+    CHK(check_built(t));
     hipStream_t st = (hipStream_t)stream;
     if (st != t->stream) t->strayed = true;
     if (!t->cfg.graph) return backward_chain(t, q, w, field_fwd, grad_q, grad_pos, st);
@@ -1490,6 +1504,7 @@ fmm_status fmm_backward(fmm_tree *t, const void *q, const void *w, const void *f
 fmm_status fmm_tree_info(const fmm_tree *tc, fmm_tree_info_t *info) {
     if (!tc || !info) return fail(FMM_EINVAL, "tree and info are required");
     fmm_tree *t = const_cast<fmm_tree *>(tc);
+    CHK(check_built(t));
     std::memset(info, 0, sizeof(*info));
     info->levels = t->L;
     info->p = t->cfg.p;
@@ -1563,6 +1578,7 @@ fmm_status fmm_stage_times_reset(fmm_tree *t) {
 
 fmm_status fmm_tree_export(const fmm_tree *t, uint32_t *perm, uint32_t *leaf_start) {
     if (!t) return fail(FMM_EINVAL, "tree is NULL");
+    CHK(check_built(t));
     if (perm) HIPCHK(hipMemcpyAsync(perm, t->perm.p, sizeof(uint32_t) * t->n, hipMemcpyDeviceToHost, t->stream));
     if (leaf_start)
         HIPCHK(hipMemcpyAsync(leaf_start, t->ad ? t->ad->lstart.p : t->start.p, sizeof(uint32_t) * (t->nleaf + 1),
@@ -1575,6 +1591,7 @@ fmm_status fmm_tree_export_adaptive(const fmm_tree *t, int64_t *sizes, int32_t *
                                     int64_t *list_start, int32_t *items) {
     if (!t || !sizes) return fail(FMM_EINVAL, "tree and sizes are required");
     if (!t->ad) return fail(FMM_EINVAL, "not an adaptive tree");
+    CHK(check_built(t));
     const AdTree *a = t->ad;
     const int64_t nbox = a->nbox;
     hipStream_t st = t->stream;
