@@ -586,6 +586,16 @@ void release(fmm_tree *t, Buf &b, hipStream_t st) {
     b.cap = 0;
 }
 
+// Wait for all work on device `dev`, whichever is current (a tree can be
+// released while another device is).
+void wait_device(int dev) {
+    int cur = dev;
+    (void)hipGetDevice(&cur);
+    if (cur != dev) (void)hipSetDevice(dev);
+    (void)hipDeviceSynchronize();
+    if (cur != dev) (void)hipSetDevice(cur);
+}
+
 // Lay buffers of the given sizes one after another, 256-byte aligned, in
 // `area` (grown through the tree's allocator where it is too small; what it
 // held is then lost, and the buffers are empty where it cannot grow).  One
@@ -1690,7 +1700,7 @@ void fmm_tree_destroy(fmm_tree *t) {
     hipStream_t st = t->stream;
     // the memory goes back in order on the build's stream: work that another
     // stream was given on the tree ends first
-    if (t->strayed) (void)hipDeviceSynchronize();
+    if (t->strayed) wait_device(t->dev);
     for (Buf *b : {&t->parts, &t->levels, &t->work, &t->pairs}) release(t, *b, st);
     if (t->ad) {
         for (Buf &b : t->ad->area) release(t, b, st);

@@ -94,3 +94,28 @@ assert build(cfg, 3000, h) == fmm.FMM_OK
 assert not any(calls())
 L.fmm_tree_destroy(h)
 """, int(adaptive), int(graph), failing)
+
+
+@pytest.mark.parametrize("adaptive", [False, True])
+@pytest.mark.parametrize("other", [False, True])
+def test_destroy_waits_for_the_trees_device(runtime, adaptive, other):
+    """A tree that another stream has used is destroyed while another device
+    is current: its own device is waited for, once, and the caller's stays
+    current.  A tree used on its build's stream alone is not waited for."""
+    _run(runtime, """
+adaptive, other = (int(x) for x in sys.argv[2:])
+h = ctypes.c_void_p()
+cfg = fmm.make_config(p=4, leaf_max=8, precision="fp64", adaptive=bool(adaptive), allocator="library")
+counts(adaptive, 3000, 585, 3)
+rt.hipSetDevice(2)
+assert build(cfg, 3000, h) == fmm.FMM_OK
+assert L.fmm_evaluate(h, P, P, P, fmm.VEC_FIELD, B if other else A) == fmm.FMM_OK
+rt.hipSetDevice(1)
+seen = len(rt.rt_calls())
+L.fmm_tree_destroy(h)
+calls = rt.rt_calls()[seen:].decode().split()
+assert [c for c in calls if c.startswith("wait")] == (["wait2"] if other else []), calls
+d = ctypes.c_int()
+rt.hipGetDevice(ctypes.byref(d))
+assert d.value == 1
+""", int(adaptive), int(other))
