@@ -694,6 +694,7 @@ fmm_status rec(fmm_tree *t, int stage, hipStream_t st) {
 // clearing: every kernel writes each element before any kernel reads it.
 fmm_status work_buffers(fmm_tree *t, bool far, bool scratch, hipStream_t st, Work &w) {
     const WorkSizes z = work_sizes(t, far);
+    const bool f64 = is_f64_form(t);
     size_t off = 0;
     auto take = [&](size_t bytes) -> size_t {
         const size_t at = off;
@@ -708,10 +709,16 @@ fmm_status work_buffers(fmm_tree *t, bool far, bool scratch, hipStream_t st, Wor
             oM[l] = take(z.M[l]);
             oL[l] = take(z.Lc[l]);
         }
-        // in the scratch array the adaptive tree's operands lie over the near
-        // and far partials where they fit: M2L ends before either is written
-        if (scratch && t->ad && z.pack[l] && z.pack[l] <= o_far + z.farf)
-            oP[l] = o_near;
+        // The adaptive tree's operands lie over the near and far partials
+        // where they fit (FP64 form; mixed form, in the scratch array): M2L
+        // ends before either is written, but for the near ones on the side
+        // stream.  Else the FP64 form reorders the multipoles in their place,
+        // so that its operands take no memory of their own.
+        const size_t over = !scratch && t->cfg.overlap_near ? o_far : o_near;
+        if (t->ad && z.pack[l] && (scratch || f64) && z.pack[l] <= o_far + z.farf - over)
+            oP[l] = over;
+        else if (t->ad && f64)
+            oP[l] = oM[l];
         else if (z.pack[l])
             oP[l] = take(z.pack[l]);
     }
@@ -1037,15 +1044,16 @@ fmm_status build_adaptive(fmm_tree *t, int64_t n, int32_t dtype, const void *pos
                                    : 1;
     if (!f64 && at != a->nvbox) return fail(FMM_EDEVICE, "internal: M2L groups do not cover the boxes");
     if (f64) {
-        // tiles of the folded M2L; its partial sums and the multipoles in K
-        // order together take at most min(8 T, max(1024, T)) tiles of 128
-        // targets' sums, T the tiles of 128 (about four parts per compute
-        // unit, and no parts above 1024 tiles)
+        // tiles of the folded M2L; its partial sums take at most what the
+        // mixed form's take in FP64, at least min(8 T, 4 ncu) tiles of 128
+        // targets, T the tiles without groups (with them at most G more), and
+        // none where there are four tiles per compute unit, less the room of
+        // the multipoles in K order
         const int tt = fold_tile_targets(c.p);
-        const int64_t T = (a->nvbox + 127) / 128;
+        const int64_t T = (a->nvbox + 127) / 128, G = 8 * std::max(nlev - 2, 0);
         const size_t sums = sizeof(double) * 128 * (size_t)c.p * c.p,
                      pack = sizeof(double) * (size_t)(nbox + 1) * coef_stride(c.p),
-                     most = T < 1024 ? sums * (size_t)std::min<int64_t>(8 * T, 1024) : 0;
+                     most = T + G < 4 * t->ncu ? sums * (size_t)std::min<int64_t>(8 * T, 4 * t->ncu) : 0;
         a->fold = fold_plan(c.p, (a->nvbox + tt - 1) / tt, t->ncu, most > pack ? most - pack : 0);
     }
     if (ngrp) {

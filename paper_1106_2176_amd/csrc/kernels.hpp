@@ -294,9 +294,10 @@ hipError_t launch_m2l_fold(int P, int L, void *const *B, void *const *Lc, const 
                            double *partial, size_t partial_bytes, int ncu, size_t cap, hipStream_t st);
 
 // m2l_fold_ad.hip: adds the adaptive tree's FP64 M2L over the V slots (in
-// fold order) into Lc; pack: nbox + 1 rows for the multipoles in K order,
-// partial: fold_partial_bytes() of the plan
-hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const FoldDev &fd, const double *M,
+// fold order) into Lc; pack: nbox + 1 rows for the multipoles in K order, or M
+// itself (its rows are then reordered in place and back), partial:
+// fold_partial_bytes() of the plan
+hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const FoldDev &fd, double *M,
                               const int *vidx, const uint32_t *code, int64_t box2, int64_t nbox, double *Lc,
                               double *pack, double *partial, hipStream_t st);
 

@@ -116,13 +116,50 @@ __global__ __launch_bounds__(256) void k_ad_fold_pack(int P, int64_t nrow, const
     out[i] = v;
 }
 
-hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const FoldDev &fd, const double *M,
+// The rows 0 .. nrow - 1 of M into K order in their place (BACK: into the
+// coefficients' own order again), the last row zero: a block reads and writes
+// reorder_rows(P) rows, four elements a thread.  Where the operands have no
+// room of their own: two passes over M in place of k_ad_fold_pack's one
+// (206,000 boxes at p = 4: 9.9 and 10.8 us against 9.4; 24,000 at p = 14: 14.1
+// and 15.7 against 14.5).
+constexpr int kReorder = 4;  // elements per thread
+static int reorder_rows(int P) { return 256 * kReorder / coef_stride(P); }
+static_assert(kMaxStride <= 256 * kReorder, "a row per block");
+template <bool BACK>
+__global__ __launch_bounds__(256) void k_ad_fold_reorder(int P, int rows, int64_t nrow,
+                                                         const int16_t *__restrict__ kperm, double *M) {
+    const int S = coef_stride(P);
+    const int64_t r0 = (int64_t)blockIdx.x * rows;
+    double *row[kReorder], v[kReorder];
+    int to[kReorder];  // where the thread's elements go, -1: none
+#pragma unroll
+    for (int k = 0; k < kReorder; ++k) {
+        const int e = threadIdx.x + 256 * k, lr = e / S, i = e - lr * S;
+        const int64_t r = r0 + lr;
+        const bool in = lr < rows && r < nrow;
+        const int c = in ? kperm[i] : -1;  // no coefficient past p^2, in either order
+        row[k] = M + r * S;
+        to[k] = in ? (BACK && c >= 0 ? c : i) : -1;
+        v[k] = r + 1 < nrow && c >= 0 ? row[k][BACK ? i : c] : 0.0;
+    }
+    __syncthreads();  // the rows have been read
+#pragma unroll
+    for (int k = 0; k < kReorder; ++k)
+        if (to[k] >= 0) row[k][to[k]] = v[k];
+}
+
+hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const FoldDev &fd, double *M,
                               const int *vidx, const uint32_t *code, int64_t box2, int64_t nbox, double *Lc,
                               double *pack, double *partial, hipStream_t st) {
     const int64_t nv = nbox - box2;
     if (nv <= 0) return hipSuccess;
     const int64_t np = (nbox + 1) * (coef_stride(P) / 2);
-    k_ad_fold_pack<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(P, nbox + 1, fd.kperm, M, (f64x2 *)pack);
+    const int rows = reorder_rows(P);
+    const unsigned nr = (unsigned)((nbox + rows) / rows);
+    if (pack == M)
+        k_ad_fold_reorder<false><<<nr, 256, 0, st>>>(P, rows, nbox + 1, fd.kperm, M);
+    else
+        k_ad_fold_pack<<<(unsigned)((np + 255) / 256), 256, 0, st>>>(P, nbox + 1, fd.kperm, M, (f64x2 *)pack);
     const unsigned nb = (unsigned)(pl.nfull + (int64_t)pl.nrest * pl.nsplit);
     switch (P) {
 #define CASE(PP)                                                                                                   \
@@ -138,6 +175,7 @@ hipError_t ad_launch_m2l_fold(int P, const FoldPlan &pl, const double *A, const 
     if (pl.nrest)
         k_ad_m2l_fold_sum<<<(unsigned)(((int64_t)pl.nrest * pl.tile * P * P + 255) / 256), 256, 0, st>>>(
             P, pl, box2, nv, partial, Lc);
+    if (pack == M) k_ad_fold_reorder<true><<<nr, 256, 0, st>>>(P, rows, nbox + 1, fd.kperm, M);
     return hipGetLastError();
 }
 
