@@ -9,6 +9,7 @@
 #include <new>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "fold.hpp"
@@ -70,9 +71,9 @@ struct HostKit {
     unsigned int *words_dev = nullptr;  // their address for kernels
     hipEvent_t ev = nullptr;            // after the copy of the build counters
 };
-constexpr size_t kKits = 8;
+constexpr int kKits = 8;
 std::mutex g_kit_mu;
-std::vector<HostKit> g_kits;
+HostKit g_kits[kKits];  // no words: an empty place
 
 void kit_free(HostKit &k) {
     if (k.ev) (void)hipEventDestroy(k.ev);
@@ -83,10 +84,9 @@ void kit_free(HostKit &k) {
 hipError_t kit_get(int dev, HostKit &k) {
     {
         std::lock_guard<std::mutex> g(g_kit_mu);
-        for (size_t i = 0; i < g_kits.size(); ++i)
-            if (g_kits[i].dev == dev) {
-                k = g_kits[i];
-                g_kits.erase(g_kits.begin() + (long)i);
+        for (HostKit &h : g_kits)
+            if (h.words && h.dev == dev) {
+                std::swap(k, h);
                 return hipSuccess;
             }
     }
@@ -103,11 +103,11 @@ void kit_put(HostKit &k, bool idle) {
     if (!k.words) return;
     if (idle) {
         std::lock_guard<std::mutex> g(g_kit_mu);
-        if (g_kits.size() < kKits) {
-            g_kits.push_back(k);
-            k = HostKit{};
-            return;
-        }
+        for (HostKit &h : g_kits)
+            if (!h.words) {
+                std::swap(k, h);
+                return;
+            }
     }
     kit_free(k);
 }

@@ -119,3 +119,21 @@ d = ctypes.c_int()
 rt.hipGetDevice(ctypes.byref(d))
 assert d.value == 1
 """, int(adaptive), int(other))
+
+
+def test_destroy_allocates_nothing(runtime):
+    """Destroying trees needs no host memory (nothing may be thrown out of
+    the C interface); words and events are handed on to at most eight later
+    trees, the others' given back."""
+    _run(runtime, """
+cfg = fmm.make_config(p=4, leaf_max=8, precision="fp64", allocator="library")
+trees = [ctypes.c_void_p() for _ in range(10)]
+for h in trees:
+    counts(False, 3000)
+    assert build(cfg, 3000, h) == fmm.FMM_OK
+rt.rt_no_memory(1)
+for h in trees:
+    L.fmm_tree_destroy(h)
+rt.rt_no_memory(0)
+assert rt.rt_calls().count(b"unpin") == 2
+""")
