@@ -211,6 +211,32 @@ def measure(fmm, wl, pos, q, precision, steps, warmup, sync, **kw):
             "build_ms": build_s * 1e3, "phi": phi.clone(), "E": E.clone()}
 
 
+def fold_flop(p):
+    """FLOP of the FP64 M2L's matrix products per target box: its offsets
+    folded by reflections into 56 products (fold.hpp) of the p^2 rows, padded
+    to fours within a parity, and K in chunks of 8; the 30 with a zero axis
+    take half of the chunks of opposite parities."""
+    count = [0] * 8
+    for n in range(p):
+        for m in range(n + 1):
+            for sine in range(2 if m else 1):
+                count[((m + sine) & 1) | (sine << 1) | (((n + m) & 1) << 2)] += 1
+    rows = sum(4 * ((c + 3) // 4) for c in count)
+    chunks = (p * p + 7) // 8
+    paired = sum(2 * min(count[k], count[7 - k]) for k in range(4)) // 8
+    return 2.0 * rows * 8 * (26 * chunks + 30 * (chunks - paired) + 15 * paired)
+
+
+def fold_roofline(kernel, runs, p, boxes, m2l_pairs, ms):
+    """The FP64 M2L's roofline: the FLOP of the products it runs, and the
+    rate that the 2 p^4 FLOP per pair of the unfolded products would need."""
+    flop = fold_flop(p) * boxes
+    tf = flop / (ms * 1e-3) / 1e12
+    return {"kernel": kernel, "kernel_run": runs, "bound": "mfma", "achieved": tf, "peak": PEAK_FP64_TFLOPS,
+            "unit": "TFLOP/s", "frac": tf / PEAK_FP64_TFLOPS, "traffic": None, "ms": ms, "flop_per_launch": flop,
+            "unfolded_tflops": 2.0 * p ** 4 * m2l_pairs / (ms * 1e-3) / 1e12}
+
+
 def rooflines(wl, res, precision, enc, on_profiled):
     """(dominant-kernel roofline, the other one) of a measured form."""
     info, dom = res["info"], res["dom"]
@@ -228,10 +254,9 @@ def rooflines(wl, res, precision, enc, on_profiled):
     if not f64:
         p2p["peak_unpacked"] = PEAK_FP32_UNPACKED_TFLOPS
         p2p["frac_unpacked"] = p2p_tf / PEAK_FP32_UNPACKED_TFLOPS
-    if f64:  # the dense products' FLOP; the folded kernel (k_m2l_fold) does 56/189 of them
-        m2l = {"kernel": "k_m2l_f64<%d>" % wl.p, "bound": "mfma", "achieved": m2l_tf,
-               "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s", "frac": m2l_tf / PEAK_FP64_TFLOPS,
-               "traffic": None}
+    if f64:  # "kernel" is the record's name for the FP64 M2L, "kernel_run" the kernel
+        m2l = fold_roofline("k_m2l_f64<%d>" % wl.p, "k_m2l_fold<%d>" % wl.p, wl.p,
+                            sum(8 ** l for l in range(2, info["levels"] + 1)), m2l_pairs, m2l_ms)
     else:
         opts, products = ENCODINGS[enc]
         nparts = 2 if opts.get("m2l_fp16") else opts["bf16_splits"]
@@ -239,8 +264,8 @@ def rooflines(wl, res, precision, enc, on_profiled):
                "bound": "mfma", "achieved": m2l_tf, "peak": PEAK_16BIT_MFMA_TFLOPS, "unit": "TFLOP/s",
                "frac": m2l_tf / PEAK_16BIT_MFMA_TFLOPS,
                "traffic": traffic_from_profile("m2l.hip", "m2l_%s_C2_counters.txt" % enc) if on_profiled else None,
-               "encoding": enc, "mfma_products_per_term": products}
-    m2l.update({"ms": m2l_ms, "flop_per_launch": 2.0 * wl.p ** 4 * m2l_pairs})
+               "encoding": enc, "mfma_products_per_term": products,
+               "ms": m2l_ms, "flop_per_launch": 2.0 * wl.p ** 4 * m2l_pairs}
     return (m2l, p2p) if dom == "M2L" else (p2p, m2l)
 
 
@@ -262,15 +287,14 @@ def sampled_errors(res, q_np, t_idx, phi_d, E_d):
 
 def adaptive_rooflines(p, res):
     """(dominant, other) rooflines of the adaptive tree's M2L (folded FP64
-    MFMA, 2 p^4 FLOP per V entry) and P2P (FP64, 19 FLOP per pair)."""
+    MFMA) and P2P (FP64, 19 FLOP per pair)."""
     info, st = res["info"], res["stages_ms"]
     m2l_ms = res["dom_ms"] if res["dom"] == "M2L" else st["M2L"]
     p2p_ms = res["dom_ms"] if res["dom"] == "P2P" else st["P2P"]
-    m2l_tf = 2.0 * p ** 4 * info["m2l_pairs"] / (m2l_ms * 1e-3) / 1e12
     p2p_tf = P2P_FLOP_PER_PAIR * info["p2p_pairs"] / (p2p_ms * 1e-3) / 1e12
-    m2l = {"kernel": "k_ad_m2l_fold<%d>" % p, "bound": "mfma", "achieved": m2l_tf, "peak": PEAK_FP64_TFLOPS,
-           "unit": "TFLOP/s", "frac": m2l_tf / PEAK_FP64_TFLOPS, "traffic": None, "ms": m2l_ms,
-           "flop_per_launch": 2.0 * p ** 4 * info["m2l_pairs"]}
+    name = "k_ad_m2l_fold<%d>" % p
+    # the targets: every box but the root and its eight children
+    m2l = fold_roofline(name, name, p, info["n_boxes"] - 9, info["m2l_pairs"], m2l_ms)
     p2p = {"kernel": "k_ad_p2p", "bound": "alu", "achieved": p2p_tf, "peak": PEAK_FP64_TFLOPS,
            "unit": "TFLOP/s", "frac": p2p_tf / PEAK_FP64_TFLOPS, "traffic": None, "ms": p2p_ms,
            "flop_per_launch": P2P_FLOP_PER_PAIR * info["p2p_pairs"]}
