@@ -20,8 +20,9 @@
  *    uses them has completed.  "host" pointers are ordinary CPU memory.
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *    fmm_build_tree blocks once, until two counters (the level-selection
- *    maximum and the count of invalid positions) have reached the host; the
- *    rest of the build stays queued on `stream`.  fmm_evaluate and
+ *    maximum and the count of invalid positions) have reached the host (an
+ *    adaptive tree's twice, see `adaptive`); the rest of the build stays
+ *    queued on `stream`.  fmm_evaluate and
  *    fmm_backward are asynchronous on `stream`.  A tree is used by one stream
  *    at a time.
  *  - Every call returns an fmm_status; after a non-OK status the outputs are
@@ -149,8 +150,9 @@ typedef struct {
                                   U/V/W/X lists of the adaptive FMM: U(b), b a
                                   leaf: b and the leaves touching it (P2P); V(b):
                                   the children of the colleagues of b's parent
-                                  not touching b (M2L, the dense FP64 product
-                                  on the matrix cores); W(b), b a leaf: the
+                                  not touching b (M2L, matrix products in FP64
+                                  with the offsets folded by reflections, see
+                                  below for the mixed form); W(b), b a leaf: the
                                   descendants of b's colleagues that do not
                                   touch b but whose parent does (the multipole
                                   evaluated at b's particles, M2P); X(b): the
@@ -166,10 +168,9 @@ typedef struct {
                                   terms (FP32 per particle and box, summed
                                   in FP64).
                                   fmm_backward runs the transposed chain over
-                                  the same lists; the build
-                                  blocks once per tree level and once more at
-                                  the end, until a few counts have reached the
-                                  host. */
+                                  the same lists; the build blocks twice, until
+                                  the boxes per level and then the lengths of
+                                  the lists have reached the host. */
     int32_t reserved[1];       /* zero */
 } fmm_config;
 
@@ -224,8 +225,9 @@ typedef struct {
  * when the predicted one's fullest leaf exceeds leaf_max), exclusive scan of
  * leaf counts, stable counting sort (ties keep input order) and a gather of
  * leaf-relative coordinates.  An adaptive tree (cfg.adaptive) sorts at
- * max_level, then builds its boxes level by level and its lists; it waits
- * for the host once per level and once more at the end.
+ * max_level, then finds the boxes of all levels in one pass over the sorted
+ * particles, and its lists; it waits for the host after the boxes are counted
+ * and after the lists are.
  * Errors: FMM_EINVAL, FMM_EDOMAIN (detected at the synchronisation; a
  * coordinate equal to lo + size is clamped into the last box), FMM_ENOMEM
  * (the allocator callback returned NULL, or hipMallocAsync failed),
@@ -278,7 +280,8 @@ fmm_status fmm_evaluate(fmm_tree *tree, const void *q, void *phi, void *vec, int
  *   - A tree whose evaluation needs more scratch than the array holds is
  *     rejected with FMM_EINVAL before any launch (the message gives the
  *     size).  Roughly: 64 B per particle plus the coefficient and M2L grids
- *     of the levels, e.g. N <= 10^5 at p = 10, leaf_max = 64.
+ *     of the levels, e.g. N <= 10^5 at p = 10, leaf_max = 64; an adaptive
+ *     tree 64 B per particle plus 16 B per coefficient of a box.
  *   - Every call on one device uses that device's one array, which keeps
  *     the last call's contents; nothing in it needs clearing.  Calls that
  *     overlap on one device (on different streams or host threads) race

@@ -118,14 +118,14 @@ struct Ops {
     // [8][P2][P2] input-major transfer tables
     double *up64 = nullptr, *down64 = nullptr, *aup64 = nullptr, *adown64 = nullptr;
     float *up32 = nullptr, *down32 = nullptr, *aup32 = nullptr, *adown32 = nullptr;
-    // M2L tables (316 operators + a zero one) of the mixed form: three bf16
-    // parts [3][317][R/16][S/8][16][8] (a 16-row tile stored piece by piece,
-    // so that the mixed kernel's copy of four pieces of a row tile reads one
-    // contiguous kilobyte); forward and adjoint
     // FP64 form: the folded M2L's tables (fold.hpp), forward and adjoint, and
     // its orders
     double *fold64 = nullptr, *afold64 = nullptr;
     FoldDev fold{};
+    // M2L tables (316 operators + a zero one) of the mixed form: three bf16
+    // parts [3][317][R/16][S/8][16][8] (a 16-row tile stored piece by piece,
+    // so that the mixed kernel's copy of four pieces of a row tile reads one
+    // contiguous kilobyte); forward and adjoint
     uint16_t *m2lbf = nullptr, *am2lbf = nullptr;
     size_t bf_part = 0;  // elements per bf16 (and binary16) part
     // binary16 encoding: a_r T rho_c in two binary16 parts, same layout as

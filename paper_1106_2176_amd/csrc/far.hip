@@ -486,8 +486,10 @@ __device__ __forceinline__ float block_level_max(int P, int l, const Tin *__rest
 // OWN_MAX: each block finds its level's maximum itself (and the level's first
 // block stores it for the M2L) instead of reading what k_level_max left: one
 // launch less in the chain, for up to kOwnMax coefficients a level, which
-// every block then reads from L2 (1e4 particles, p = 4, 512 leaves: 9.6 us in
-// two kernels, 7.1 in one).
+// every block then reads from L2.  An evaluation with two kernels and with
+// one, us: 8,192 coefficients (p = 4, 512 leaves) 49.6 and 47.1; 12,800 (p =
+// 14, 64 leaves) 127.0 and 125.6; 16,384 (p = 5, 512) 54.6 and 54.2; 20,480
+// (p = 6, 512) 58.1 and 59.3; 53,248 (p = 10, 512) 91.1 and 100.
 constexpr int64_t kOwnMax = 16384;
 template <typename Tout, bool OWN_MAX>
 __global__ __launch_bounds__(256) void k_pack(int P, PackPlan pl) {

@@ -152,9 +152,10 @@ hipError_t ad_launch_vslots(int64_t box2, int64_t nb, const AdBoxes &bx, const i
 hipError_t ad_launch_lists(int64_t nbox, bool fill, const AdBoxes &bx, const int *col, uint32_t *nu, uint32_t *nw,
                            uint32_t *nx, const uint32_t *ou, const uint32_t *ow, const uint32_t *ox, int *iu,
                            int *iw, int *ix, hipStream_t st);
-// per-box list offsets ou/ow/ox [nbox + 1] from the three per-(box,
-// direction) scans stored one after another, each 27 nbox + 1 long; host[0..2]
-// = the list lengths, host[3..] = nsplit[nlev], then ccnt[ngrp]
+// per-box list offsets ou/ow/ox [nbox + 1] from one scan of the U, W and X
+// counts per (box, direction) stored one after another (s27[81 nbox + 1], list
+// k from s27[27 nbox k] on); host[0..2] = the list lengths, host[3..] =
+// nsplit[nlev], then ccnt[ngrp]
 hipError_t ad_launch_box_offsets(int64_t nbox, const uint32_t *s27, uint32_t *ou, uint32_t *ow, uint32_t *ox,
                                  int nlev, const unsigned int *nsplit, int ngrp, const unsigned int *ccnt,
                                  unsigned int *host, hipStream_t st);

@@ -2,11 +2,11 @@
 // adaptive tree: the boxes of levels >= 2 are one list of targets, their
 // sources the rows that their V slots name.  Targets need no grouping by
 // level or class (the operators serve all of them).
-// Measured, 1e6 particles in Gaussian blobs, p = 8 (50,906 boxes): 1.12 ms
-// against 2.92 ms of the direct products (v_mfma_f64_16x16x4_f64, 189 slots);
-// the matrix products alone would take 0.31 ms, the rest is the signs,
+// Measured, 1e6 particles in Gaussian blobs, p = 8 (60,559 boxes): 1.07
+// ms against 2.92 ms of the direct products (v_mfma_f64_16x16x4_f64, 189
+// slots); the matrix products alone would take 0.31 ms, the rest is the signs,
 // butterflies and addresses, which do not run beside them, and waiting for
-// the sources (0.88 ms without a source read 0.63, on a full grid).
+// the sources (with every source read left out, 28% less).
 #include "fold_kernel.hpp"
 
 namespace fmm {
