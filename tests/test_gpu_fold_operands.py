@@ -99,3 +99,20 @@ def test_whole_tiles_match_the_oracle(oracle_mod, p, n):
     assert rel_l2(E.cpu().numpy(), ref["E"]) < 1e-10
     assert rel_l2(far.cpu().numpy(), ref["phi_far"]) < 1e-10
     assert rel_l2(E_far.cpu().numpy(), ref["E_far"]) < 1e-10
+
+
+@pytest.mark.parametrize("p,n,leaf,adaptive", [(2, 3000, 20, False), (8, 12_000, 12, False), (12, 3000, 20, False),
+                                               (16, 3000, 20, False), (8, 20_000, 32, True)])
+def test_the_folded_products_round_like_the_direct_ones(oracle_mod, p, n, leaf, adaptive):
+    """The far field of charges of both signs against the oracle.  A local
+    coefficient sums up to 189 p^2 = 48,384 products; their roundings (1.1e-16
+    each, of either sign) and the oracle's give about sqrt(48,384) 1.1e-16 =
+    2.4e-14 of the terms' size at most: 1e-13 rel-L2."""
+    pos, q = inputs.clustered(n, 505) if adaptive else inputs.particles(n, 505, "u11")
+    q = q - q.mean()
+    ref = oracle_mod.fmm_adaptive(pos, q, p, leaf) if adaptive else oracle_mod.fmm(pos, q, p, leaf)
+    with fmm.Tree(dev(pos), p=p, leaf_max=leaf, precision="fp64", adaptive=adaptive, max_level=10) as t:
+        phi, E = t.evaluate(dev(q), part="far")
+        torch.cuda.synchronize()
+    assert rel_l2(phi.cpu().numpy(), ref["phi_far"]) < 1e-13
+    assert rel_l2(E.cpu().numpy(), ref["E_far"]) < 1e-13
